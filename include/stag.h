@@ -40,7 +40,8 @@
  * Memory: the library allocates its workspace in stag_create, on the first
  *   solve that needs more shift vectors than any earlier one, and on the first
  *   use of an optional feature (compressed or FP32/FP16 link copies, the FP32
- *   Krylov workspace, trajectory staging buffers, captured iteration graphs);
+ *   Krylov workspace, trajectory staging buffers, the exchange area of the
+ *   one-launch solves, captured iteration graphs);
  *   it never allocates inside an iteration.
  */
 #ifndef STAG_H
@@ -538,7 +539,12 @@ stag_status stag_profile_samples(stag_handle h, int kind, float* us_out, int cap
  * round trip before the arithmetic of each.  mode 1 (default): on lattices
  * whose Dslash grid (Vh / 64 blocks) is at most 512 blocks, where iterations
  * are latency-bound; 2: at every size; 0: never (the three-launch loop).
- * The two loops solve the same systems to the same tolerance; their reduction
+ * Mode 1 goes one step further on lattices of at most one 64-site tile per
+ * compute unit (Vh <= 16384) without the improved operator: the whole solve is
+ * one cooperative launch (resident.hip) that keeps the links in registers,
+ * unless profiling is on, the launch is refused or a wait inside it exceeds one
+ * second (the loop above then does the solve, and the later ones).
+ * All loops solve the same systems to the same tolerance; their reduction
  * trees differ, so results agree to rounding, not bitwise.  Returns
  * STAG_ERR_INVALID_ARG for a mode outside 0..2. */
 stag_status stag_set_fused_iteration(stag_handle h, int mode);

@@ -249,6 +249,7 @@ stag_status stag_create(stag_handle* out, const int dims[4], void* hip_stream) {
     if (c->tps != 1 && c->tps != 2 && c->tps != 4) c->tps = 2;
     if (const char* e = std::getenv("STAG_CHUNK")) c->chunk = std::max(1, std::atoi(e));
     if (const char* e = std::getenv("STAG_FUSED")) c->fused = std::max(0, std::min(2, std::atoi(e)));
+    if (const char* e = std::getenv("STAG_RESIDENT_WAIT_US")) c->res_wait = 100ull * std::max(0, std::atoi(e));
     if (const char* e = std::getenv("STAG_LINK_NT")) c->link_nt = std::max(0, std::min(2, std::atoi(e)));
     c->user = (hipStream_t)hip_stream;
     auto bail = [&](stag_status s) {
@@ -311,7 +312,7 @@ stag_status stag_destroy(stag_handle c) {
                     c->naik_w3, c->r32, c->p32, c->p2_32, c->Ap32, c->w32,
                     c->links, c->links_backup, c->mom, c->r, c->p, c->p2, c->Ap, c->w_o, c->tmp_e, c->tmp_o, c->xi,
                     c->phi, c->pool_x, c->pool_p, c->pool_y, c->st, c->dpart, c->qpart[0], c->qpart[1],
-                    c->gpart, c->scal, c->mom_tmp, c->mom_aux, c->mom_judge};
+                    c->gpart, c->scal, c->mom_tmp, c->mom_aux, c->mom_judge, c->xch};
     for (void* b : bufs)
         if (b) hipFree(b);
     if (c->st_host) hipHostFree(c->st_host);

@@ -264,6 +264,7 @@ struct MsState {
     MsIter fin;         // copy of the state at termination
     double true_res2[kMaxPoles];  // |b - (A+sigma_k) x_k|^2 (final check)
     MsHist hist[kLagMax];         // scalars of iteration i at hist[i % lag]
+    int aborted;                  // resident solver: a wait between blocks timed out, results void
 };
 
 // Pointer bundles passed by value to kernels.

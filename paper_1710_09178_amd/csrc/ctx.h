@@ -43,6 +43,7 @@ struct stag_ctx {
     double2* p2 = nullptr;   // second search direction (the fused loop double-buffers p)
     float2* p2_32 = nullptr; // the same for FP32 Krylov vectors
     double2 *xi = nullptr, *phi = nullptr;
+    void* xch = nullptr;  // exchange area of the resident solver (first use)
     // FP32 Krylov workspace (precision form)
     float2 *r32 = nullptr, *p32 = nullptr, *Ap32 = nullptr, *w32 = nullptr;
     double2* pool_x = nullptr;   // n_cap even vectors: solutions
@@ -63,6 +64,8 @@ struct stag_ctx {
     int lag = 8;                         // shift-update window of the multi-shift solver
     int use_graph = 1;                   // replay iteration chunks from captured hipGraphs
     int fused = 1;                       // FP64 solves fold the base update into the D_oe launch
+    int resident = 1;                    // one-launch solves where the lattice fits (0: a wait timed out)
+    unsigned long long res_wait = 100000000;  // ... after this many ticks of the 100 MHz clock
     int link_nt = 1;                     // non-temporal FP64 link loads: 0 never, 1 by field size, 2 always
     // captured iteration chunks, keyed by every argument their launches take
     struct ChunkGraph {

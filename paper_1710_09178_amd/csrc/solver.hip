@@ -7,6 +7,7 @@
 
 #include "ctx.h"
 #include "msfused.h"
+#include "resident.h"
 
 namespace stag {
 
@@ -553,6 +554,58 @@ uint64_t solve_kind(const MsState* h, bool fused, bool fp64, int naik, int fmt64
     return x;
 }
 
+// One launch of the resident solver (resident.hip) on the state in c->st: a new
+// solve of source b, or (b = NULL) max_steps further steps of the CG in r, p.
+// Reads the state back into c->st_host.  done = false: it could not be launched
+// or a wait inside it timed out; c->resident is then off and the outputs are
+// undefined.  after(): work enqueued behind the launch.
+template <class V, class After>
+stag_status run_resident(stag_ctx* c, const LinkSet& ls, const double2* b, VecPtrs X, VecPtrs P, int max_steps,
+                         After after, bool& done) {
+    const MsState* h = c->st_host;
+    const Krylov<V> K(c);
+    ResidentArgs<V> a{};
+    a.b = b;
+    a.r = K.r;
+    a.p = K.p;
+    a.x = X;
+    a.ps = P;
+    a.st = c->st;
+    a.xch = c->xch;
+    a.n = h->n;
+    a.base = h->base;
+    a.lag = h->lag;
+    a.max_steps = max_steps;
+    a.mt = h->mass_term;
+    a.wait = c->res_wait;
+    done = launch_resident<V>(c->g, ls, a, c->s) == hipSuccess;
+    if (!done) (void)hipGetLastError();
+    if (done) after();
+    HIP_OR_FAIL(c, hipMemcpyAsync(c->st_host, c->st, sizeof(MsState), hipMemcpyDeviceToHost, c->s));
+    HIP_OR_FAIL(c, hipStreamSynchronize(c->s));
+    done = done && !c->st_host->aborted;
+    if (!done) c->resident = 0;
+    return STAG_OK;
+}
+
+// Exchange area of the resident solver; false (and off) where it cannot be had.
+bool ensure_exchange(stag_ctx* c) {
+    if (c->xch) return true;
+    if (hipMalloc(&c->xch, resident_bytes(c->g)) == hipSuccess) return true;
+    (void)hipGetLastError();
+    c->xch = nullptr;
+    c->resident = 0;
+    return false;
+}
+
+// Is the resident solver the one to use?  On the lattices it holds a CG
+// iteration takes 4-7 us where the fused loop takes 12-14 us (8^4: 5.2 against
+// 11.9 us, 16^3x8: 7.2 against 14.1 us, 12 poles, whole solve over iterations).
+bool resident_ready(stag_ctx* c, const LinkSet& ls, bool fp64) {
+    return c->fused == 1 && c->lag >= 2 && c->resident && !c->prof_on && resident_fits(c->g, ls, fp64) &&
+           ensure_exchange(c);
+}
+
 template <class V>
 stag_status ms_solve_t(stag_ctx* c, const LinkSet& ls, double mass, const stag_rational* r, double tol, int maxiter,
                        const double2* b, double2* const* x, int* ipp_out, SolveResult& res, EvRec& rec) {
@@ -562,38 +615,50 @@ stag_status ms_solve_t(stag_ctx* c, const LinkSet& ls, double mass, const stag_r
     if (e != STAG_OK) return e;
     HIP_OR_FAIL(c, hipStreamSynchronize(c->s));  // st_host is reused
     MsState* h = c->st_host;
-    int base;
-    init_state(h, n, r->pole, r->residue, r->c0, mass, tol, maxiter, base);
-    // the fused loop (window >= 2; it keeps r_{j-1} and r_j in the ring
-    // at once): by default on grids of at most kFusedMaxBlocks Dslash blocks,
-    // where an iteration is latency-bound; with on = 2 at every size
-    const bool fused = c->lag >= 2 &&
-                       (c->fused == 2 || (c->fused == 1 && dslash_fused_grid(g) <= kFusedMaxBlocks));
-    h->lag = fused ? c->lag : (n > 1 ? c->lag : 1);
-    HIP_OR_FAIL(c, hipMemcpyAsync(c->st, h, sizeof(MsState), hipMemcpyHostToDevice, c->s));
     Krylov<V> K(c);
     VecPtrs X{}, P{};
     for (int k = 0; k < n; ++k) {
         X.p[k] = x[k];
         P.p[k] = (V*)c->pool_p + (size_t)k * 3 * g.vh;
     }
-    launch_ms_init<V>(g, b, K.r, K.p, X, P, c->st, c->qpart[0], c->s);
-    res.fused = fused;
-    // the iterations of the last solve of this kind, as the chunk scheduler's
-    // estimate (a hint only: the solve runs until its own stop)
-    const uint64_t kind = solve_kind(h, fused, sizeof(V) == sizeof(double2), c->naik, ls.fmt64, ls.fmt32);
-    const auto hint = c->iter_hint.find(kind);
-    const int pred = hint == c->iter_hint.end() ? 0 : hint->second;
-    if (fused)
-        e = run_fused<V>(c, ls, K, X, P, c->chunk, rec, pred);
-    else
-        e = run_iterations<V>(c, ls, K, X, P, c->chunk, rec, [](int) {}, true, false, pred);
-    if (e) return e;
-    HIP_OR_FAIL(c, hipMemcpyAsync(h, c->st, sizeof(MsState), hipMemcpyDeviceToHost, c->s));
-    HIP_OR_FAIL(c, hipStreamSynchronize(c->s));
+    constexpr bool fp64 = sizeof(V) == sizeof(double2);
+    int base;
+    bool solved = false;
+    // one launch per solve where the lattice fits the chip, a launch loop
+    // otherwise: with window >= 2 (the fused loop keeps r_{j-1} and r_j in the
+    // ring at once) the fused one on grids of at most kFusedMaxBlocks Dslash
+    // blocks, where an iteration is latency-bound; with on = 2 at every size
+    if (resident_ready(c, ls, fp64)) {
+        init_state(h, n, r->pole, r->residue, r->c0, mass, tol, maxiter, base);
+        h->lag = c->lag;
+        HIP_OR_FAIL(c, hipMemcpyAsync(c->st, h, sizeof(MsState), hipMemcpyHostToDevice, c->s));
+        res.fused = false;
+        if ((e = run_resident<V>(c, ls, b, X, P, -1, []() {}, solved))) return e;
+    }
+    if (!solved) {
+        init_state(h, n, r->pole, r->residue, r->c0, mass, tol, maxiter, base);
+        const bool fused = c->lag >= 2 &&
+                           (c->fused == 2 || (c->fused == 1 && dslash_fused_grid(g) <= kFusedMaxBlocks));
+        h->lag = fused ? c->lag : (n > 1 ? c->lag : 1);
+        HIP_OR_FAIL(c, hipMemcpyAsync(c->st, h, sizeof(MsState), hipMemcpyHostToDevice, c->s));
+        launch_ms_init<V>(g, b, K.r, K.p, X, P, c->st, c->qpart[0], c->s);
+        res.fused = fused;
+        // the iterations of the last solve of this kind, as the chunk scheduler's
+        // estimate (a hint only: the solve runs until its own stop)
+        const uint64_t kind = solve_kind(h, fused, fp64, c->naik, ls.fmt64, ls.fmt32);
+        const auto hint = c->iter_hint.find(kind);
+        const int pred = hint == c->iter_hint.end() ? 0 : hint->second;
+        if (fused)
+            e = run_fused<V>(c, ls, K, X, P, c->chunk, rec, pred);
+        else
+            e = run_iterations<V>(c, ls, K, X, P, c->chunk, rec, [](int) {}, true, false, pred);
+        if (e) return e;
+        HIP_OR_FAIL(c, hipMemcpyAsync(h, c->st, sizeof(MsState), hipMemcpyDeviceToHost, c->s));
+        HIP_OR_FAIL(c, hipStreamSynchronize(c->s));
+        c->iter_hint[kind] = h->fin.iter;
+    }
     const MsIter& f = h->fin;
     res.iters = f.iter;
-    c->iter_hint[kind] = f.iter;
     res.nonfinite = f.nonfinite;
     res.bb = f.bb;
     res.converged = 1;
@@ -643,6 +708,8 @@ stag_status refine_pole(stag_ctx* c, const LinkSet& ls, double mass, double pole
         int base;
         const double one = 1.0;
         init_state(h, 1, &pole, &one, 0.0, mass, tol, maxiter - iters_out, base);
+        const bool resident = resident_ready(c, ls, false);
+        if (resident) h->lag = 2;  // (no shifts: the window only sizes buffers)
         h->bb_given = 1;
         h->it[0].bb = bb;
         HIP_OR_FAIL(c, hipMemcpyAsync(c->st, h, sizeof(MsState), hipMemcpyHostToDevice, c->s));
@@ -650,11 +717,22 @@ stag_status refine_pole(stag_ctx* c, const LinkSet& ls, double mass, double pole
         launch_cg_restart(g, K.r, K.p, c->qpart[0], c->s);
         VecPtrs X{}, P{};
         X.p[0] = x;
-        stag_status e = run_iterations<float2>(
-            c, ls, K, X, P, every, rec, [&](int par_next) { reliable(c->qpart[par_next]); }, false, true);
-        if (e) return e;
-        HIP_OR_FAIL(c, hipMemcpyAsync(h, c->st, sizeof(MsState), hipMemcpyDeviceToHost, c->s));
-        HIP_OR_FAIL(c, hipStreamSynchronize(c->s));
+        stag_status e = STAG_OK;
+        if (resident) {
+            bool ok = true;
+            do {
+                if ((e = run_resident<float2>(c, ls, nullptr, X, P, every,
+                                              [&]() { reliable(c->gpart + 4 * (size_t)nbr); }, ok)))
+                    return e;
+            } while (ok && !h->done[0]);
+            if (!ok) continue;  // (a wait timed out) start again from the residual of what x holds
+        } else {
+            e = run_iterations<float2>(
+                c, ls, K, X, P, every, rec, [&](int par_next) { reliable(c->qpart[par_next]); }, false, true);
+            if (e) return e;
+            HIP_OR_FAIL(c, hipMemcpyAsync(h, c->st, sizeof(MsState), hipMemcpyDeviceToHost, c->s));
+            HIP_OR_FAIL(c, hipStreamSynchronize(c->s));
+        }
         iters_out += h->fin.iter;
         if (h->fin.nonfinite) return fail(c, STAG_ERR_NONFINITE, "non-finite value in the refinement CG");
         // the step kernel may have stopped on a recursive residual: check in FP64

@@ -529,7 +529,8 @@ class Lattice:
         self._check(self.lib.stag_set_shift_window(self.h, int(lag)))
 
     def set_fused_iteration(self, mode):
-        """0 / False: three-launch loop; 1 / True: fused on small grids (default); 2: fused at every size."""
+        """0 / False: three-launch loop; 1 / True (default): one launch per solve on the smallest lattices, fused
+        loop on small grids, three launches above; 2: fused loop at every size."""
         self._check(self.lib.stag_set_fused_iteration(self.h, int(mode)))
 
     def set_link_streaming(self, mode: int):
