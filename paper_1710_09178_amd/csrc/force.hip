@@ -15,12 +15,6 @@ __device__ __forceinline__ M3 load_link(const double2* __restrict__ links, const
     return m;
 }
 
-__device__ __forceinline__ M3 load_link_at(const double2* __restrict__ links, const Geom& g, int x, int y, int z,
-                                           int t, int mu) {
-    const int par = (x + y + z + t) & 1;
-    return load_link(links, g, par, cb_index(g, x, y, z, t), mu);
-}
-
 __device__ __forceinline__ void store_force(double* __restrict__ mom, const Geom& g, int par, int mu, int cb,
                                             const double f[8], double dt) {
     double* m = mom + mom_off(g, par, mu, 0) + cb;
@@ -197,49 +191,104 @@ __global__ __launch_bounds__(kBlock) void k_naik_force3(Geom g, const double2* _
     for (int a = 0; a < 8; ++a) m[(size_t)a * g.vh] += fac * f[a];
 }
 
-// F_a = -(beta/3) Im tr(T_a U_mu(x) A_mu(x)), A = sum of the six staples.
-__global__ __launch_bounds__(kBlock) void k_gauge_force(Geom g, const double2* __restrict__ links, double beta,
-                                                        double* __restrict__ mom, double dt) {
-    const int V = 2 * g.vh;
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= 4 * V) return;
-    const int mu = i / V, rem = i % V;
-    const int par = rem / g.vh, cb = rem % g.vh;
+// The tile and parity of a block of a kernel that takes 64 sites of one parity
+// per block: consecutive blocks of an XCD take both parities of one tile, and
+// the tiles of an XCD are a z-slab (xcd_tile_slab), so that the links its blocks
+// share are read into one L2.
+template <int SB>
+__device__ __forceinline__ void tile_of_block(const Geom& g, int ntiles, int& tile, int& par) {
+    const int b = blockIdx.x, full = ntiles / 8 * 16;  // blocks of whole rounds of 8 tiles
+    if (b < full) {
+        par = (b >> 3) & 1;
+        tile = (b >> 4) * 8 + (b & 7);
+    } else {
+        par = (b - full) & 1;
+        tile = ntiles / 8 * 8 + (b - full) / 2;
+    }
+    tile = xcd_tile_slab(tile, ntiles, g, SB);
+}
+
+struct Site {
     int x, y, z, t;
-    cb_coords(g, par, cb, x, y, z, t);
-    const int n[4] = {g.nx, g.ny, g.nz, g.nt};
-    int c[4] = {x, y, z, t};
+};
+template <int MU>
+__device__ __forceinline__ Site step_up(const Geom& g, Site s) {
+    if (MU == 0) s.x = (s.x + 1 == g.nx) ? 0 : s.x + 1;
+    if (MU == 1) s.y = (s.y + 1 == g.ny) ? 0 : s.y + 1;
+    if (MU == 2) s.z = (s.z + 1 == g.nz) ? 0 : s.z + 1;
+    if (MU == 3) s.t = (s.t + 1 == g.nt) ? 0 : s.t + 1;
+    return s;
+}
+template <int MU>
+__device__ __forceinline__ Site step_down(const Geom& g, Site s) {
+    if (MU == 0) s.x = (s.x == 0) ? g.nx - 1 : s.x - 1;
+    if (MU == 1) s.y = (s.y == 0) ? g.ny - 1 : s.y - 1;
+    if (MU == 2) s.z = (s.z == 0) ? g.nz - 1 : s.z - 1;
+    if (MU == 3) s.t = (s.t == 0) ? g.nt - 1 : s.t - 1;
+    return s;
+}
+__device__ __forceinline__ int index_of(const Geom& g, Site s) { return cb_index(g, s.x, s.y, s.z, s.t); }
+
+// A += the upper and the lower staple of link (s, MU) in the plane (MU, NU)
+template <int MU, int NU>
+__device__ __forceinline__ void add_staples(const Geom& g, const double2* __restrict__ links, int par, Site s, M3& A) {
+    if constexpr (MU != NU) {
+        const Site up = step_up<MU>(g, s), dn = step_down<NU>(g, s);
+        // upper: U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
+        const M3 a1 = load_link(links, g, par ^ 1, index_of(g, up), NU);
+        const M3 a2 = load_link(links, g, par ^ 1, index_of(g, step_up<NU>(g, s)), MU);
+        const M3 a3 = load_link(links, g, par, index_of(g, s), NU);
+        A = m3_add(A, m3_mul(m3_mul(a1, m3_dag(a2)), m3_dag(a3)));
+        // lower: U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu)
+        const M3 b1 = load_link(links, g, par, index_of(g, step_down<NU>(g, up)), NU);
+        const M3 b2 = load_link(links, g, par ^ 1, index_of(g, dn), MU);
+        const M3 b3 = load_link(links, g, par ^ 1, index_of(g, dn), NU);
+        A = m3_add(A, m3_mul(m3_mul(m3_dag(b1), m3_dag(b2)), b3));
+    }
+}
+template <int MU>
+__device__ __forceinline__ void gauge_force_link(const Geom& g, const double2* __restrict__ links, double beta,
+                                                 double* __restrict__ mom, double dt, int par, int cb) {
+    Site s;
+    cb_coords(g, par, cb, s.x, s.y, s.z, s.t);
     M3 A;
 #pragma unroll
     for (int e = 0; e < 9; ++e) A.e[e] = make_double2(0.0, 0.0);
-    for (int nu = 0; nu < 4; ++nu) {
-        if (nu == mu) continue;
-        int cp[4] = {c[0], c[1], c[2], c[3]};  // x + mu
-        cp[mu] = (c[mu] + 1 == n[mu]) ? 0 : c[mu] + 1;
-        int cn[4] = {c[0], c[1], c[2], c[3]};  // x + nu
-        cn[nu] = (c[nu] + 1 == n[nu]) ? 0 : c[nu] + 1;
-        int cm[4] = {c[0], c[1], c[2], c[3]};  // x - nu
-        cm[nu] = (c[nu] == 0) ? n[nu] - 1 : c[nu] - 1;
-        int cpm[4] = {cp[0], cp[1], cp[2], cp[3]};  // x + mu - nu
-        cpm[nu] = cm[nu];
-        // upper: U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
-        const M3 a1 = load_link_at(links, g, cp[0], cp[1], cp[2], cp[3], nu);
-        const M3 a2 = load_link_at(links, g, cn[0], cn[1], cn[2], cn[3], mu);
-        const M3 a3 = load_link_at(links, g, c[0], c[1], c[2], c[3], nu);
-        A = m3_add(A, m3_mul(m3_mul(a1, m3_dag(a2)), m3_dag(a3)));
-        // lower: U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu)
-        const M3 b1 = load_link_at(links, g, cpm[0], cpm[1], cpm[2], cpm[3], nu);
-        const M3 b2 = load_link_at(links, g, cm[0], cm[1], cm[2], cm[3], mu);
-        const M3 b3 = load_link_at(links, g, cm[0], cm[1], cm[2], cm[3], nu);
-        A = m3_add(A, m3_mul(m3_mul(m3_dag(b1), m3_dag(b2)), b3));
-    }
-    const M3 U = load_link(links, g, par, cb, mu);
+    add_staples<MU, 0>(g, links, par, s, A);
+    add_staples<MU, 1>(g, links, par, s, A);
+    add_staples<MU, 2>(g, links, par, s, A);
+    add_staples<MU, 3>(g, links, par, s, A);
+    const M3 U = load_link(links, g, par, cb, MU);
     double f[8];
     im_tr_ta(m3_mul(U, A), f);
     const double fac = -beta / 3.0;
 #pragma unroll
     for (int a = 0; a < 8; ++a) f[a] *= fac;
-    store_force(mom, g, par, mu, cb, f, dt);
+    store_force(mom, g, par, MU, cb, f, dt);
+}
+
+// F_a = -(beta/3) Im tr(T_a U_mu(x) A_mu(x)), A = sum of the six staples.  One
+// wave per direction and 64 sites of one parity: the direction and the plane are
+// constants of the code, and the four waves of a block read 76 links of which
+// many are the same or their neighbours', from one L1 and one L2.  Bound by the
+// L2: 23 million 128-byte requests at 32^3x8, 17 TB/s, 171 us (436 us with one
+// thread per link in (direction, parity, site) order, where the directions of a
+// site are a launch's length apart).  Tried: three waves per SIMD (168
+// registers, 17 of them spilled) 177 us; one wave per plane, whose two links
+// share the upper loop and whose traces are summed in LDS, 25% fewer requests
+// but 186 registers in blocks of six waves, one block per CU, 215 us.
+__global__ __launch_bounds__(kBlock) void k_gauge_force(Geom g, const double2* __restrict__ links, double beta,
+                                                        double* __restrict__ mom, double dt, int ntiles) {
+    int tile, par;
+    tile_of_block<64>(g, ntiles, tile, par);
+    const int cb = tile * 64 + (threadIdx.x & 63);
+    if (cb >= g.vh) return;
+    switch (threadIdx.x >> 6) {
+        case 0: gauge_force_link<0>(g, links, beta, mom, dt, par, cb); break;
+        case 1: gauge_force_link<1>(g, links, beta, mom, dt, par, cb); break;
+        case 2: gauge_force_link<2>(g, links, beta, mom, dt, par, cb); break;
+        default: gauge_force_link<3>(g, links, beta, mom, dt, par, cb); break;
+    }
 }
 
 // exp(i X) for Hermitian X: scaling and squaring with a degree-12 Taylor
@@ -340,30 +389,45 @@ __global__ __launch_bounds__(kBlock) void k_link_update(Geom g, double2* __restr
     for (int e = 0; e < 9; ++e) u[(size_t)e * g.vh] = R.e[e];
 }
 
-// sum over sites and mu<nu of Re tr P_{mu nu}(x)
+// Re tr of the plaquette (MU, NU) at s; um = U_MU(s)
+template <int MU, int NU>
+__device__ __forceinline__ double plaq_retr(const Geom& g, const double2* __restrict__ links, int par, Site s,
+                                            const M3& um, const M3& un) {
+    const M3 a = load_link(links, g, par ^ 1, index_of(g, step_up<MU>(g, s)), NU);
+    const M3 b = load_link(links, g, par ^ 1, index_of(g, step_up<NU>(g, s)), MU);
+    const M3 l = m3_mul(um, a), r = m3_mul(un, b);
+    double t = 0.0;  // Re tr(l r^dag)
+#pragma unroll
+    for (int e = 0; e < 9; ++e) t += l.e[e].x * r.e[e].x + l.e[e].y * r.e[e].y;
+    return t;
+}
+
+// Sum of Re tr over the six plaquettes of each site.  Two waves take the three
+// planes with x and two the other three, for 64 sites each of a 128-site tile;
+// a plane costs two products and a trace.  Bound by the one read of the links:
+// 302 MB at 32^3x8 in 39 us (131 us with one thread per site, three products
+// per plane and the planes in a loop).
 __global__ __launch_bounds__(kBlock) void k_plaquette(Geom g, const double2* __restrict__ links,
-                                                      double* __restrict__ part) {
-    const int V = 2 * g.vh;
-    const int i = blockIdx.x * kBlock + threadIdx.x;
+                                                      double* __restrict__ part, int ntiles) {
+    int tile, par;
+    tile_of_block<128>(g, ntiles, tile, par);
+    const int cb = tile * 128 + (threadIdx.x & 127);
     double acc[1] = {0.0};
-    if (i < V) {
-        const int par = i / g.vh, cb = i % g.vh;
-        int c[4];
-        cb_coords(g, par, cb, c[0], c[1], c[2], c[3]);
-        const int n[4] = {g.nx, g.ny, g.nz, g.nt};
-        for (int mu = 0; mu < 4; ++mu) {
-            int cp[4] = {c[0], c[1], c[2], c[3]};
-            cp[mu] = (c[mu] + 1 == n[mu]) ? 0 : c[mu] + 1;
-            const M3 umu = load_link(links, g, par, cb, mu);
-            for (int nu = mu + 1; nu < 4; ++nu) {
-                int cn[4] = {c[0], c[1], c[2], c[3]};
-                cn[nu] = (c[nu] + 1 == n[nu]) ? 0 : c[nu] + 1;
-                const M3 a = load_link_at(links, g, cp[0], cp[1], cp[2], cp[3], nu);
-                const M3 b = load_link_at(links, g, cn[0], cn[1], cn[2], cn[3], mu);
-                const M3 d = load_link(links, g, par, cb, nu);
-                const M3 P = m3_mul(m3_mul(umu, a), m3_dag(m3_mul(d, b)));
-                acc[0] += P.e[0].x + P.e[4].x + P.e[8].x;
-            }
+    if (cb < g.vh) {
+        Site s;
+        cb_coords(g, par, cb, s.x, s.y, s.z, s.t);
+        const M3 u1 = load_link(links, g, par, cb, 1);
+        if (threadIdx.x < 128) {
+            const M3 u0 = load_link(links, g, par, cb, 0);
+            acc[0] = plaq_retr<0, 1>(g, links, par, s, u0, u1);
+            acc[0] += plaq_retr<0, 2>(g, links, par, s, u0, load_link(links, g, par, cb, 2));
+            acc[0] += plaq_retr<0, 3>(g, links, par, s, u0, load_link(links, g, par, cb, 3));
+        } else {
+            const M3 u2 = load_link(links, g, par, cb, 2);
+            acc[0] = plaq_retr<1, 2>(g, links, par, s, u1, u2);
+            const M3 u3 = load_link(links, g, par, cb, 3);
+            acc[0] += plaq_retr<1, 3>(g, links, par, s, u1, u3);
+            acc[0] += plaq_retr<2, 3>(g, links, par, s, u2, u3);
         }
     }
     block_partial<1>(acc, part);
@@ -413,8 +477,8 @@ void launch_naik_force3(const Geom& g, const double2* links, VecPtrs X, VecPtrs 
 }
 
 void launch_gauge_force(const Geom& g, const double2* links, double beta, double* mom, double dt, hipStream_t s) {
-    const int grid = (8 * g.vh + kBlock - 1) / kBlock;
-    k_gauge_force<<<grid, kBlock, 0, s>>>(g, links, beta, mom, dt);
+    const int ntiles = (g.vh + 63) / 64;
+    k_gauge_force<<<2 * ntiles, kBlock, 0, s>>>(g, links, beta, mom, dt, ntiles);
 }
 
 void launch_link_update(const Geom& g, double2* links, const double* mom, double dt, hipStream_t s) {
@@ -423,9 +487,9 @@ void launch_link_update(const Geom& g, double2* links, const double* mom, double
 }
 
 int launch_plaquette(const Geom& g, const double2* links, double* part, hipStream_t s) {
-    const int grid = (2 * g.vh + kBlock - 1) / kBlock;
-    k_plaquette<<<grid, kBlock, 0, s>>>(g, links, part);
-    return grid;
+    const int ntiles = (g.vh + 127) / 128;
+    k_plaquette<<<2 * ntiles, kBlock, 0, s>>>(g, links, part, ntiles);
+    return 2 * ntiles;
 }
 
 int launch_kinetic(const Geom& g, const double* mom, double* part, hipStream_t s) {
