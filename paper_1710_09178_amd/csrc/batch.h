@@ -49,7 +49,6 @@ struct BState {
     unsigned long long* t_done;  // [n_sys] device wall clock at the stop
     double* sigma0_term;  // [n_inst] 4 m_i^2 + sigma_0
     int lag;              // shift-update window (1..kLagMax); residual ring of `lag` vectors
-    MsHist* hist;         // [n_sys][kLagMax] scalars of the pending iterations
     size_t ring_stride;   // entries between ring slots (one batched vector)
     BScal* scal;          // [n_sys] this iteration's scalars (written by the scalar kernel)
     double* w_tab;        // [n_sys][3][kWinTab] alpha_s, beta_s, zeta_s of the window's iterations

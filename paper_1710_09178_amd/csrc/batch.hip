@@ -77,91 +77,94 @@ __device__ __forceinline__ void bhop_geometry(const Geom& g, int mu, int x, int 
     }
 }
 
-// ---- epilogues over (rhs, colour, site) items of one tile
+// Epilogues of the operator, one call per entry (right-hand side rh, colour,
+// site) at index i of a batched vector; K sums per right-hand side go to
+// part[tile][kMaxRhs][K].
 template <class V>
 struct BEpiStore {
-    static constexpr int K = 1;
+    static constexpr int K = 0;
+    double* part;  // (unused)
     V* out;
-    __device__ __forceinline__ void item(const BInst& I, int, int R, int rh, int site, int c, V v,
-                                         double (&)[K]) const {
-        out[bvec_off(I, R, rh, c) + site] = v;
-    }
-    __device__ __forceinline__ void finish(int, double (&)[K]) const {}
+    __device__ __forceinline__ void item(const BInst&, int, size_t i, V v, double*) const { out[i] = v; }
 };
 
 // Ap = (4 m_i^2 + sigma_0) p - v and per-rhs partials of <p,Ap>, <r,Ap>, <Ap,Ap>
 template <class V>
 struct BEpiCG {
-    static constexpr int K = 3 * kMaxRhs;
+    static constexpr int K = 3;
+    double* part;
     V* Ap;
     const V* p;
     const V* r;
     const double* sigma0_term;  // [inst] 4 m_i^2 + sigma_0
-    double* part;  // [tile][kMaxRhs][3]
-    __device__ __forceinline__ void item(const BInst& I, int inst, int R, int rh, int site, int c, V v,
-                                         double (&acc)[K]) const {
-        const size_t i = bvec_off(I, R, rh, c) + site;
+    __device__ __forceinline__ void item(const BInst&, int inst, size_t i, V v, double* acc) const {
         const V pv = p[i], rv = r[i];
         using Rl = typename BPrec<V>::R;
         const Rl m = (Rl)sigma0_term[inst];
         const V a = V{m * pv.x - v.x, m * pv.y - v.y};
         Ap[i] = a;
         const double2 pd = to_d2(pv), rd = to_d2(rv), ad = to_d2(a);
-        const double d0 = pd.x * ad.x + pd.y * ad.y, d1 = rd.x * ad.x + rd.y * ad.y, d2 = ad.x * ad.x + ad.y * ad.y;
-#pragma unroll
-        for (int q = 0; q < kMaxRhs; ++q) {  // selects: no dynamic register indexing
-            acc[3 * q + 0] += (q == rh) ? d0 : 0.0;
-            acc[3 * q + 1] += (q == rh) ? d1 : 0.0;
-            acc[3 * q + 2] += (q == rh) ? d2 : 0.0;
-        }
-    }
-    __device__ __forceinline__ void finish(int tile, double (&acc)[K]) const {
-        double v[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) v[k] = acc[k];
-        __shared__ double lds[4 * K];
-        block_sum<K>(v, lds);
-        if (threadIdx.x == 0)
-#pragma unroll
-            for (int k = 0; k < K; ++k) part[(size_t)tile * K + k] = v[k];
+        acc[0] += pd.x * ad.x + pd.y * ad.y;
+        acc[1] += rd.x * ad.x + rd.y * ad.y;
+        acc[2] += ad.x * ad.x + ad.y * ad.y;
     }
 };
 
-// FP64 residual b - ((4 m_i^2 + pole) x - v): per-rhs partials of |res|^2
+// r = b - (A_i + pole) x with per-rhs |r|^2 partials; r stored when rout != null
 struct BEpiResid {
-    static constexpr int K = kMaxRhs;
+    static constexpr int K = 1;
+    double* part;
     const double2* x;
     const double2* b;
     double2* rout;
     double pole;
-    double* part;  // [tile][kMaxRhs]
-    __device__ __forceinline__ void item(const BInst& I, int, int R, int rh, int site, int c, double2 v,
-                                         double (&acc)[K]) const {
-        const size_t i = bvec_off(I, R, rh, c) + site;
+    __device__ __forceinline__ void item(const BInst& I, int, size_t i, double2 v, double* acc) const {
         const double coef = I.four_m2 + pole;
         const double2 xv = x[i], bv = b[i];
         const double rx = bv.x - (coef * xv.x - v.x), ry = bv.y - (coef * xv.y - v.y);
         if (rout) rout[i] = make_double2(rx, ry);
-#pragma unroll
-        for (int q = 0; q < kMaxRhs; ++q)
-            if (q == rh) acc[q] += rx * rx + ry * ry;
+        acc[0] += rx * rx + ry * ry;
     }
-    __device__ __forceinline__ void finish(int tile, double (&acc)[K]) const {
-        double v[K];
+};
+
+// Sums of a block whose threads take entries of any right-hand side.
+template <class Epi>
+struct BlockSums {
+    static constexpr int N = Epi::K * kMaxRhs;
+    double acc[N > 0 ? N : 1];
+    __device__ __forceinline__ BlockSums() {
 #pragma unroll
-        for (int k = 0; k < K; ++k) v[k] = acc[k];
-        __shared__ double lds[4 * K];
-        block_sum<K>(v, lds);
-        if (threadIdx.x == 0)
+        for (int k = 0; k < N; ++k) acc[k] = 0.0;
+    }
+    template <class V>
+    __device__ __forceinline__ void item(const Epi& epi, const BInst& I, int inst, int rh, size_t i, V v) {
+        double d[Epi::K + 1] = {};
+        epi.item(I, inst, i, v, d);
 #pragma unroll
-            for (int k = 0; k < K; ++k) part[(size_t)tile * K + k] = v[k];
+        for (int q = 0; q < kMaxRhs; ++q)  // selects: no dynamic register indexing
+#pragma unroll
+            for (int k = 0; k < Epi::K; ++k) acc[q * Epi::K + k] += (q == rh) ? d[k] : 0.0;
+    }
+    __device__ __forceinline__ void finish(const Epi& epi, int tile) {
+        if constexpr (N > 0) {
+            __shared__ double lds[4 * N];
+            block_sum<N>(acc, lds);
+            if (threadIdx.x == 0)
+#pragma unroll
+                for (int k = 0; k < N; ++k) epi.part[(size_t)tile * N + k] = acc[k];
+        }
     }
 };
 
 // One block per tile: TPS threads per site split the 4 directions; every
-// thread applies its links to all right-hand sides of the lattice.
+// thread applies its links to all right-hand sides of the lattice.  At 9 lattices
+// of 70,848 sites together and 4 right-hand sides the four-thread form misses
+// the L2 for 155 MB (storing) and 184 MB (CG epilogue) of the 109 and 136 MB that
+// it cannot do without, at 6 TB/s: 24 and 27 us (26 and 33 us before the tiles
+// of a lattice were put in neighbour order and the waves finished a right-hand
+// side each).  A fourth wave per SIMD (128 registers, 12 spilled) gains nothing.
 template <int TPS, class V, class Epi, bool NT, bool L12>
-__global__ __launch_bounds__(kBlock) void k_bdslash(BatchDev bd, const V* __restrict__ links, const V* __restrict__ in,
+__global__ __launch_bounds__(kBlock, TPS == 4 ? 3 : 2) void k_bdslash(BatchDev bd, const V* __restrict__ links, const V* __restrict__ in,
                                                     int out_par, Epi epi, const int* __restrict__ inst_done) {
     constexpr int SB = kBlock / TPS;
     constexpr int DPT = 4 / TPS;
@@ -171,7 +174,8 @@ __global__ __launch_bounds__(kBlock) void k_bdslash(BatchDev bd, const V* __rest
     const BInst I = bd.inst[tl.inst];
     const Geom& g = I.g;
     const int R = bd.nrhs;
-    __shared__ V part[TPS * kMaxRhs * 3 * SB];
+    constexpr bool kWaveRhs = TPS == 4;  // wave r of four finishes right-hand side r
+    __shared__ V part[(kWaveRhs ? (TPS - 1) : TPS) * kMaxRhs * 3 * SB];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int slice = wave % TPS, sgrp = wave / TPS;
     const int j = sgrp * 64 + lane;
@@ -191,62 +195,123 @@ __global__ __launch_bounds__(kBlock) void k_bdslash(BatchDev bd, const V* __rest
             int cbf, cbb;
             bool nf, nb;
             bhop_geometry(g, mu, x, y, z, t, cbf, cbb, nf, nb);
-            V U[9], W[9];
             const V* uf = lk + link_off(g, out_par, mu, 0) + cb;
             const V* ub = lk + link_off(g, 1 - out_par, mu, 0) + cbb;
             constexpr int NE = L12 ? 6 : 9;
+            // one matrix at a time, so that four waves fit on a SIMD
+            {
+                V U[9];
 #pragma unroll
-            for (int e = 0; e < NE; ++e) U[e] = bload<NT>(uf + (size_t)e * g.vh);
+                for (int e = 0; e < NE; ++e) U[e] = bload<NT>(uf + (size_t)e * g.vh);
+                if constexpr (L12) brebuild_row2(U);
+                const Rl sf = nf ? Rl(-1) : Rl(1);
 #pragma unroll
-            for (int e = 0; e < NE; ++e) W[e] = bload<NT>(ub + (size_t)e * g.vh);
-            if constexpr (L12) {
-                brebuild_row2(U);
-                brebuild_row2(W);
-            }
-            const Rl sf = nf ? Rl(-1) : Rl(1);
-            const Rl sb = nb ? Rl(-1) : Rl(1);
+                for (int r = 0; r < kMaxRhs; ++r) {
+                    if (r >= R) break;
+                    V pf[3];
 #pragma unroll
-            for (int r = 0; r < kMaxRhs; ++r) {
-                if (r >= R) break;
-                V pf[3], pb[3];
+                    for (int c = 0; c < 3; ++c) pf[c] = in[bvec_off(I, R, r, c) + cbf];
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    pf[c] = in[bvec_off(I, R, r, c) + cbf];
-                    pb[c] = in[bvec_off(I, R, r, c) + cbb];
+                    for (int a = 0; a < 3; ++a) {
+                        V f = cmul(U[3 * a], pf[0]);
+                        f = cadd(f, cmul(U[3 * a + 1], pf[1]));
+                        f = cadd(f, cmul(U[3 * a + 2], pf[2]));
+                        acc[r][a].x += sf * f.x;
+                        acc[r][a].y += sf * f.y;
+                    }
                 }
+            }
+            {
+                V W[9];
 #pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    V f = cmul(U[3 * a], pf[0]);
-                    f = cadd(f, cmul(U[3 * a + 1], pf[1]));
-                    f = cadd(f, cmul(U[3 * a + 2], pf[2]));
-                    V bb = cmulc(W[a], pb[0]);
-                    bb = cadd(bb, cmulc(W[3 + a], pb[1]));
-                    bb = cadd(bb, cmulc(W[6 + a], pb[2]));
-                    acc[r][a].x += sf * f.x - sb * bb.x;
-                    acc[r][a].y += sf * f.y - sb * bb.y;
+                for (int e = 0; e < NE; ++e) W[e] = bload<NT>(ub + (size_t)e * g.vh);
+                if constexpr (L12) brebuild_row2(W);
+                const Rl sb = nb ? Rl(-1) : Rl(1);
+#pragma unroll
+                for (int r = 0; r < kMaxRhs; ++r) {
+                    if (r >= R) break;
+                    V pb[3];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) pb[c] = in[bvec_off(I, R, r, c) + cbb];
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) {
+                        V bb = cmulc(W[a], pb[0]);
+                        bb = cadd(bb, cmulc(W[3 + a], pb[1]));
+                        bb = cadd(bb, cmulc(W[6 + a], pb[2]));
+                        acc[r][a].x -= sb * bb.x;
+                        acc[r][a].y -= sb * bb.y;
+                    }
                 }
             }
         }
     }
+    if constexpr (kWaveRhs) {
+        // The wave of right-hand side r keeps its own slice of it and adds the
+        // other three: a quarter less LDS (36.9 KB: four blocks per CU), and its
+        // sums need no other wave.
+        static_assert(kMaxRhs == 4, "one wave per right-hand side");
 #pragma unroll
-    for (int r = 0; r < kMaxRhs; ++r)
+        for (int r = 0; r < kMaxRhs; ++r)
+            if (r != slice && r < R)
 #pragma unroll
-        for (int c = 0; c < 3; ++c)
-            if (r < R) part[((slice * kMaxRhs + r) * 3 + c) * SB + j] = acc[r][c];
-    __syncthreads();
-    double racc[Epi::K];
+                for (int c = 0; c < 3; ++c)
+                    part[((r * 3 + (slice < r ? slice : slice - 1)) * 3 + c) * SB + lane] = acc[r][c];
+        __syncthreads();
+        if (slice >= R) return;
+        double racc[Epi::K + 1] = {};
+        if (cb < g.vh) {
+            V own[3];
 #pragma unroll
-    for (int k = 0; k < Epi::K; ++k) racc[k] = 0.0;
-    for (int it = threadIdx.x; it < R * 3 * SB; it += kBlock) {
-        const int rh = it / (3 * SB), c = (it / SB) % 3, jj = it % SB;
-        const int site = tl.cb0 + jj;
-        if (site >= g.vh) continue;
-        V v = part[((0 * kMaxRhs + rh) * 3 + c) * SB + jj];
+            for (int c = 0; c < 3; ++c) {
+                own[c] = acc[0][c];
 #pragma unroll
-        for (int s = 1; s < TPS; ++s) v = cadd(v, part[((s * kMaxRhs + rh) * 3 + c) * SB + jj]);
-        epi.item(I, tl.inst, R, rh, site, c, v, racc);
+                for (int r = 1; r < kMaxRhs; ++r)
+                    if (slice == r) own[c] = acc[r][c];
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                V v = own[c];
+                V o[3];
+#pragma unroll
+                for (int s = 0; s < 3; ++s) o[s] = part[((slice * 3 + s) * 3 + c) * SB + lane];
+                // slices in order
+                const V a0 = slice == 0 ? v : o[0];
+                const V a1 = slice == 0 ? o[0] : slice == 1 ? v : o[1];
+                const V a2 = slice <= 1 ? o[1] : slice == 2 ? v : o[2];
+                const V a3 = slice == 3 ? v : o[2];
+                v = cadd(cadd(cadd(a0, a1), a2), a3);
+                epi.item(I, tl.inst, bvec_off(I, R, slice, c) + cb, v, racc);
+            }
+        }
+        if constexpr (Epi::K > 0) {
+            double v[Epi::K];
+#pragma unroll
+            for (int k = 0; k < Epi::K; ++k) v[k] = racc[k];
+            wave_sum<Epi::K>(v);
+            if (lane == 0)
+#pragma unroll
+                for (int k = 0; k < Epi::K; ++k)
+                    epi.part[((size_t)blockIdx.x * kMaxRhs + slice) * Epi::K + k] = v[k];
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < kMaxRhs; ++r)
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                if (r < R) part[((slice * kMaxRhs + r) * 3 + c) * SB + j] = acc[r][c];
+        __syncthreads();
+        BlockSums<Epi> sums;
+        for (int it = threadIdx.x; it < R * 3 * SB; it += kBlock) {
+            const int plane = it / SB, rh = plane / 3, c = plane % 3, jj = it % SB;
+            const int site = tl.cb0 + jj;
+            if (site >= g.vh) continue;
+            V v = part[((0 * kMaxRhs + rh) * 3 + c) * SB + jj];
+#pragma unroll
+            for (int s = 1; s < TPS; ++s) v = cadd(v, part[((s * kMaxRhs + rh) * 3 + c) * SB + jj]);
+            sums.item(epi, I, tl.inst, rh, bvec_off(I, R, rh, c) + site, v);
+        }
+        sums.finish(epi, blockIdx.x);
     }
-    epi.finish(blockIdx.x, racc);
 }
 
 // Eight lanes per output site, one hop each: lane h takes direction h / 2,
@@ -302,9 +367,7 @@ __global__ __launch_bounds__(kBlock) void k_bdslash8(BatchDev bd, const V* __res
 #pragma unroll
         for (int e = 0; e < 9; ++e) U[e] = V{0, 0};
     }
-    double racc[Epi::K];
-#pragma unroll
-    for (int k = 0; k < Epi::K; ++k) racc[k] = 0.0;
+    BlockSums<Epi> sums;
 #pragma unroll
     for (int r = 0; r < kMaxRhs; ++r) {
         if (r >= R) break;
@@ -329,9 +392,9 @@ __global__ __launch_bounds__(kBlock) void k_bdslash8(BatchDev bd, const V* __res
         if (on)
 #pragma unroll
             for (int c = 0; c < 3; ++c)
-                if ((3 * r + c) % 8 == h) epi.item(I, tl.inst, R, r, cb, c, a[c], racc);
+                if ((3 * r + c) % 8 == h) sums.item(epi, I, tl.inst, r, bvec_off(I, R, r, c) + cb, a[c]);
     }
-    epi.finish(blockIdx.x, racc);
+    sums.finish(epi, blockIdx.x);
 }
 
 template <class V, class Epi>
@@ -389,7 +452,7 @@ __global__ __launch_bounds__(kBlock) void k_bms_init(BatchDev bd, const double2*
         p[i] = bl;
         for (int k = 0; k < n; ++k) {
             x.at<double2>(k)[i] = make_double2(0.0, 0.0);
-            if (k != base) ps.at<V>(k)[i] = bl;
+            if (k != base || st.lag > 1) ps.at<V>(k)[i] = bl;
         }
 #pragma unroll
         for (int q = 0; q < kMaxRhs; ++q)
@@ -401,27 +464,44 @@ __global__ __launch_bounds__(kBlock) void k_bms_init(BatchDev bd, const double2*
         for (int q = 0; q < kMaxRhs; ++q) qout[(size_t)blockIdx.x * kMaxRhs + q] = acc[q];
 }
 
-// Scalars of system s from this iteration's sums (one thread per system).
-// The shifted updates are deferred over windows of st.lag iterations as in
-// the single-lattice solver: the scalars of each iteration go to the
-// system's history, and the window's last iteration (or the stopping one)
-// applies them in order.  w_*: this system's [lag][n] window tables.  Also
-// writes the system's state for the next iteration (or the final one).
-__device__ void bsystem_scalars(BState& st, int s, int par, double rr, double pAp, double rAp, double ApAp,
-                                BScal& o, double* w_as, double* w_bs, double* w_zn, int* w_act) {
+// Scalars of system s from this iteration's sums, by one wave with one shift
+// per lane.  The shifted updates are deferred over windows of st.lag iterations
+// as in the single-lattice solver: the scalars of each iteration stay in the
+// system's [lag][n] window tables w_*, and the window's last iteration (or the
+// stopping one) applies them in order.  Also writes the system's state for the
+// next iteration (or the final one).
+static_assert(kMaxPoles <= 64, "one lane per shift");
+struct ShiftState {  // what a lane reads of the previous iteration's state
+    double z, zo, shift, bb, a_old, b_old;
+    int was, ipp, iter;
+    __device__ __forceinline__ ShiftState(const BState& st, const MsIter& S, int k) {
+        const bool on = k < st.n;
+        z = on ? S.zeta[k] : 0.0;
+        zo = on ? S.zeta_old[k] : 0.0;
+        shift = on ? st.shift[k] : 0.0;
+        was = on ? S.active[k] : 0;
+        ipp = on ? S.iters_per_pole[k] : 0;
+        bb = S.bb;
+        a_old = S.alpha_old;
+        b_old = S.beta_old;
+        iter = S.iter;
+    }
+};
+__device__ __forceinline__ void bsystem_scalars(const BState& st, int s, int par, const ShiftState& S, double rr,
+                                                double pAp, double rAp, double ApAp, BScal& o, double* w_as,
+                                                double* w_bs, double* w_zn, int* w_act) {
     const int n = st.n, base = st.base, L = st.lag;
-    const MsIter& S = st.it[par][s];
+    const int k = threadIdx.x & 63;
+    const bool on = k < n;
     const int iter = S.iter;
     const int slot = iter % L;
     const double bb = (iter == 0 && !st.bb_given) ? rr : S.bb;
+    const double a_old = S.a_old, b_old = S.b_old, z = S.z, zo = S.zo, shift = S.shift;
+    const int was = S.was, ipp = S.ipp;
+    const int act = was && !(z * z * rr <= st.tol2 * bb);
+    const unsigned long long acts = __ballot(act);
     int nonfinite = !isfinite(rr);
-    int any = 0;
-    for (int k = 0; k < n; ++k) {
-        const int a = S.active[k] && !(S.zeta[k] * S.zeta[k] * rr <= st.tol2 * bb);
-        w_act[slot * n + k] = a;
-        any |= a;
-    }
-    int stop = nonfinite || !any || iter >= st.maxiter;
+    int stop = nonfinite || !acts || iter >= st.maxiter;
     double alpha = 0.0, beta = 0.0;
     if (!stop) {
         alpha = rr / pAp;
@@ -433,67 +513,48 @@ __device__ void bsystem_scalars(BState& st, int s, int par, double rr, double pA
             stop = 1;
         }
     }
-    const double a_old = S.alpha_old, b_old = S.beta_old;
-    for (int k = 0; k < n; ++k) {
-        const double z = S.zeta[k], zo = S.zeta_old[k];
-        double zn = z, as = 0.0, bs = 0.0;
-        if (!stop) {
-            if (k == base) {
-                zn = 1.0;
-                as = alpha;
-                bs = beta;
-            } else if (w_act[slot * n + k]) {
-                zn = z * zo * a_old / (alpha * b_old * (zo - z) + zo * a_old * (1.0 + st.shift[k] * alpha));
-                const double q = zn / z;
-                as = alpha * q;
-                bs = beta * q * q;
-            }
+    double zn = z, as = 0.0, bs = 0.0;
+    if (!stop) {
+        if (k == base) {
+            zn = 1.0;
+            as = alpha;
+            bs = beta;
+        } else if (act) {
+            zn = z * zo * a_old / (alpha * b_old * (zo - z) + zo * a_old * (1.0 + shift * alpha));
+            const double q = zn / z;
+            as = alpha * q;
+            bs = beta * q * q;
         }
-        w_as[slot * n + k] = as;
-        w_bs[slot * n + k] = bs;
-        w_zn[slot * n + k] = zn;
     }
     const int npend = stop ? slot : slot + 1;
     const int flush = npend > 0 && (stop || slot == L - 1);
-    if (flush)
-        for (int t = 0; t < slot; ++t)
-            for (int k = 0; k < n; ++k) {
-                const MsHist& h = st.hist[(size_t)s * kLagMax + t];
-                w_as[t * n + k] = h.as[k];
-                w_bs[t * n + k] = h.bs[k];
-                w_zn[t * n + k] = h.zn[k];
-                w_act[t * n + k] = h.act[k];
-            }
-    o.alpha = alpha;
-    o.beta = beta;
-    o.stop = stop;
-    o.flush = flush;
-    o.npend = npend;
-    o.slot = slot;
-    o.base_on = !stop && w_act[slot * n + base];
-    int m = 0;
-    if (flush)
-        for (int k = 0; k < n; ++k)
-            if (k != base && w_act[k]) o.list[m++] = k;  // active at the window's first iteration
-    o.nact = m;
-    {
+    int first = act;  // active at the window's first iteration
+    if (on) {
+        if (slot > 0) first = w_act[k];
+        w_as[slot * n + k] = as;
+        w_bs[slot * n + k] = bs;
+        w_zn[slot * n + k] = zn;
+        w_act[slot * n + k] = act;
         MsIter& N = stop ? st.fin[s] : st.it[par ^ 1][s];
-        for (int k = 0; k < n; ++k) {
-            const int a = stop ? 0 : w_act[slot * n + k];
-            N.active[k] = w_act[slot * n + k];
-            N.iters_per_pole[k] = (a && !stop) ? iter + 1 : (S.active[k] ? iter : S.iters_per_pole[k]);
-            N.zeta[k] = stop ? S.zeta[k] : w_zn[slot * n + k];
-            N.zeta_old[k] = stop ? S.zeta_old[k] : S.zeta[k];
-            if (!stop && !flush) {
-                MsHist& h = st.hist[(size_t)s * kLagMax + slot];
-                h.as[k] = w_as[slot * n + k];
-                h.bs[k] = w_bs[slot * n + k];
-                h.zn[k] = w_zn[slot * n + k];
-                h.act[k] = w_act[slot * n + k];
-            }
-        }
-        N.alpha_old = stop ? S.alpha_old : alpha;
-        N.beta_old = stop ? S.beta_old : beta;
+        N.active[k] = act;
+        N.iters_per_pole[k] = (act && !stop) ? iter + 1 : (was ? iter : ipp);
+        N.zeta[k] = zn;
+        N.zeta_old[k] = stop ? zo : z;
+    }
+    const unsigned long long list = __ballot(flush && first && (k != base || L > 1));
+    if ((list >> k) & 1) o.list[__popcll(list & ((1ull << k) - 1))] = k;
+    if (k == 0) {
+        o.alpha = alpha;
+        o.beta = beta;
+        o.stop = stop;
+        o.flush = flush;
+        o.npend = npend;
+        o.slot = slot;
+        o.base_on = L == 1 && !stop && ((acts >> base) & 1);
+        o.nact = __popcll(list);
+        MsIter& N = stop ? st.fin[s] : st.it[par ^ 1][s];
+        N.alpha_old = stop ? a_old : alpha;
+        N.beta_old = stop ? b_old : beta;
         N.bb = bb;
         N.rr = rr;
         N.iter = stop ? iter : iter + 1;
@@ -505,196 +566,197 @@ __device__ void bsystem_scalars(BState& st, int s, int par, double rr, double pA
     }
 }
 
-// One block per instance: the sums over the instance's tiles (in tile
-// order) and the scalars of its systems, evaluated once per iteration instead
-// of in every tile of the step.  Reads the stop flags of parity par and
-// writes those of par ^ 1.
-__global__ __launch_bounds__(kBlock) void k_bms_scalars(BatchDev bd, BState st, const double* __restrict__ dpart,
-                                                        const double* __restrict__ qin, int par) {
+// One block per instance: the sums over the instance's tiles and the scalars
+// of its systems, evaluated once per iteration instead of in every tile of the
+// step.  Reads the stop flags of parity par and writes those of par ^ 1.  One
+// wave per right-hand side, whose sums and shifts need no other wave.  Bound by
+// a chain of dependent reads (flags, table,
+// partials, tables written): 6 us for 9 lattices x 4 right-hand sides x 12
+// shifts, every iteration (28 us, and 15 more at the end of a window, with one
+// thread per system and the window's scalars copied from a second table).
+__global__ __launch_bounds__(64 * kMaxRhs) void k_bms_scalars(BatchDev bd, BState st, const double* __restrict__ dpart,
+                                                              const double* __restrict__ qin, int par) {
     const int inst = blockIdx.x;
+    const int R = bd.nrhs;
+    const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int* done_in = st.inst_done + par * st.n_inst;
     int* done_out = st.inst_done + (par ^ 1) * st.n_inst;
+    const BInst& I = bd.inst[inst];
+    const int t0 = I.tile0, t1 = t0 + I.ntiles;
     if (done_in[inst]) {
         if (threadIdx.x == 0) done_out[inst] = 1;
         return;
     }
-    const BInst I = bd.inst[inst];
-    const int R = bd.nrhs;
-    __shared__ double lds[4 * 4 * kMaxRhs];
     __shared__ int sh_stop[kMaxRhs];
-    // sums over the lattice's tiles: [rhs] rr, [rhs][3] dots
-    double v[4 * kMaxRhs];
-#pragma unroll
-    for (int k = 0; k < 4 * kMaxRhs; ++k) v[k] = 0.0;
-    for (int t = I.tile0 + threadIdx.x; t < I.tile0 + I.ntiles; t += kBlock) {
-#pragma unroll
-        for (int q = 0; q < kMaxRhs; ++q) {
-            v[4 * q + 0] += qin[(size_t)t * kMaxRhs + q];
-            v[4 * q + 1] += dpart[(size_t)t * 3 * kMaxRhs + 3 * q + 0];
-            v[4 * q + 2] += dpart[(size_t)t * 3 * kMaxRhs + 3 * q + 1];
-            v[4 * q + 3] += dpart[(size_t)t * 3 * kMaxRhs + 3 * q + 2];
-        }
-    }
-    block_sum<4 * kMaxRhs>(v, lds);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < 4 * kMaxRhs; ++k) lds[k] = v[k];
-    }
-    __syncthreads();
-    // stopped before this launch; a stop in this launch is written to the other parity
-    const int* sys_in = st.sys_done + (size_t)par * st.n_inst * R;
-    int* sys_out = st.sys_done + (size_t)(par ^ 1) * st.n_inst * R;
-    if (threadIdx.x < R) {
-        const int q = threadIdx.x;
-        const int s = inst * R + q;
+    const int s = inst * R + q;
+    if (q < R) {
         BScal& o = st.scal[s];
-        if (sys_in[s]) {
-            sys_out[s] = 1;
-            o.stop = 1;
-            o.flush = 0;
-            o.nact = 0;
-            o.base_on = 0;
-            sh_stop[q] = 1;
+        // stopped before this launch; a stop in this launch is written to the other parity
+        if (st.sys_done[(size_t)par * st.n_inst * R + s]) {
+            if (lane == 0) {
+                st.sys_done[(size_t)(par ^ 1) * st.n_inst * R + s] = 1;
+                o.stop = 1;
+                o.flush = 0;
+                o.nact = 0;
+                o.base_on = 0;
+                sh_stop[q] = 1;
+            }
         } else {
+            const ShiftState S(st, st.it[par][s], lane);
+            double v[4] = {0.0, 0.0, 0.0, 0.0};  // rr and the three dots of the operator
+            for (int t = t0 + lane; t < t1; t += 64) {
+                v[0] += qin[(size_t)t * kMaxRhs + q];
+#pragma unroll
+                for (int d = 0; d < 3; ++d) v[1 + d] += dpart[(size_t)t * 3 * kMaxRhs + 3 * q + d];
+            }
+            wave_sum<4>(v);
             double* wt = st.w_tab + (size_t)s * 3 * kWinTab;
-            bsystem_scalars(st, s, par, lds[4 * q], lds[4 * q + 1], lds[4 * q + 2], lds[4 * q + 3], o, wt,
-                            wt + kWinTab, wt + 2 * kWinTab, st.w_act + (size_t)s * kWinTab);
-            sh_stop[q] = o.stop;
+            bsystem_scalars(st, s, par, S, v[0], v[1], v[2], v[3], o, wt, wt + kWinTab, wt + 2 * kWinTab,
+                            st.w_act + (size_t)s * kWinTab);
+            if (lane == 0) sh_stop[q] = o.stop;
         }
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         int all = 1;
-        for (int q = 0; q < R; ++q) all &= sh_stop[q];
+        for (int r = 0; r < R; ++r) all &= sh_stop[r];
         if (all) done_out[inst] = 1;
     }
 }
 
+// r, p and, at the end of a window, the shifted systems of one tile.  A wave
+// takes entries of one right-hand side only (four, two or one waves each for
+// one, two or more of them), so that the scalars, the list of shifts, their
+// vectors' addresses and the window's coefficients are the same for its lanes
+// and come by scalar loads.  Bound by its vectors: for 9 lattices of
+// 70,848 sites together, 4 right-hand sides and 12 shifts, 12 us an iteration
+// (68 MB) and 125 us with the shifts (830 MB, 6.6 TB/s); 22 and 190 us with
+// entries of any right-hand side in a wave and the coefficients in LDS.
 template <class V>
 __global__ __launch_bounds__(kBlock) void k_bms_step(BatchDev bd, V* __restrict__ ring, const V* __restrict__ Ap,
                                                      V* __restrict__ p, VecPtrs x, VecPtrs ps, BState st,
+                                                     const BScal* __restrict__ scal,
+                                                     const double* __restrict__ w_tab, const int* __restrict__ w_act,
                                                      double* __restrict__ qout, int par) {
     const BTile tl = bd.tiles[blockIdx.x];
     if (st.inst_done[par * st.n_inst + tl.inst]) return;
     const BInst I = bd.inst[tl.inst];
-    const int R = bd.nrhs, SB = bd.tile_sites, n = st.n, L = st.lag;
-    __shared__ BScal sc[kMaxRhs];
-    __shared__ double lds[4 * kMaxRhs];
-    // window tables [rhs][lag][n]: as, bs, zn (double) then act (int)
-    extern __shared__ double wdyn[];
-    const int wsz = L * n;
-    double* w_as = wdyn;
-    double* w_bs = w_as + kMaxRhs * wsz;
-    double* w_zn = w_bs + kMaxRhs * wsz;
-    int* w_act = (int*)(w_zn + kMaxRhs * wsz);
-    {
-        constexpr int words = (int)(sizeof(BScal) / sizeof(int));
-        const int* src = (const int*)(st.scal + (size_t)tl.inst * R);
-        int* dst = (int*)sc;
-        for (int w = threadIdx.x; w < R * words; w += kBlock) dst[w] = src[w];
-    }
-    __syncthreads();
-    int anyflush = 0;
-    for (int q = 0; q < R; ++q) anyflush |= sc[q].flush;
-    if (anyflush) {
-        for (int e = threadIdx.x; e < R * wsz; e += kBlock) {
-            const int q = e / wsz, j = e % wsz;
-            const size_t sy = (size_t)tl.inst * R + q;
-            const double* wt = st.w_tab + sy * 3 * kWinTab;
-            w_as[e] = wt[j];
-            w_bs[e] = wt[kWinTab + j];
-            w_zn[e] = wt[2 * kWinTab + j];
-            w_act[e] = st.w_act[sy * kWinTab + j];
-        }
-        __syncthreads();
-    }
-    double acc[kMaxRhs] = {0.0, 0.0, 0.0, 0.0};
-    const int base = st.base;
-    for (int it = threadIdx.x; it < R * 3 * SB; it += kBlock) {
-        const int rh = it / (3 * SB), c = (it / SB) % 3, jj = it % SB;
-        const int site = tl.cb0 + jj;
-        if (site >= I.g.vh) continue;
-        const BScal& S = sc[rh];
-        if (S.stop && !S.flush) continue;
-        const size_t i = bvec_off(I, R, rh, c) + site;
-        const int slot = S.slot;
-        const double2 r0 = to_d2(ring[(size_t)slot * st.ring_stride + i]);
-        double2 rv = r0;
+    const int R = bd.nrhs, SB = bd.tile_sites, n = st.n, L = st.lag, base = st.base;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int nw = R == 1 ? 4 : R == 2 ? 2 : 1;  // waves per right-hand side
+    const int rh = wave / nw;
+    __shared__ double lds[kBlock / 64];
+    double acc[1] = {0.0};
+    if (rh < R) {
+        const size_t sy = (size_t)tl.inst * R + rh;
+        const BScal& S = scal[sy];
+        const int nitem = 3 * SB, first = (wave % nw) * 64 + lane, stride = nw * 64;
+        const int lgSB = 31 - __clz(SB);  // SB is a power of two
+        const size_t off = bvec_off(I, R, rh, 0);
+        // the base system's r and p (and its x where the window is one iteration;
+        // longer windows update it with the others, which saves reading and
+        // writing it each time): kItems entries per lane with their loads in
+        // flight together
+        constexpr int kItems = 3;
         if (!S.stop) {
             const double alpha = S.alpha, beta = S.beta;
-            const double2 a = to_d2(Ap[i]);
-            const double2 pv = to_d2(p[i]);
-            rv.x -= alpha * a.x;
-            rv.y -= alpha * a.y;
-            const V rl = from_d2<V>(rv);
-            ring[(size_t)((slot + 1) % L) * st.ring_stride + i] = rl;
-            rv = to_d2(rl);
+            const V* r_in = ring + (size_t)S.slot * st.ring_stride;
+            V* r_out = ring + (size_t)((S.slot + 1) % L) * st.ring_stride;
+            for (int it0 = first; it0 < nitem; it0 += kItems * stride) {
+                V r0[kItems], a[kItems], pv[kItems];
+                double2 xv[kItems];
+                size_t idx[kItems];
+                bool on[kItems];
 #pragma unroll
-            for (int q = 0; q < kMaxRhs; ++q)
-                if (q == rh) acc[q] += rv.x * rv.x + rv.y * rv.y;
-            if (S.base_on) {
-                double2* xb = x.at<double2>(base);
-                const double2 xv = xb[i];
-                xb[i] = make_double2(xv.x + alpha * pv.x, xv.y + alpha * pv.y);
-            }
-            p[i] = from_d2<V>(make_double2(rv.x + beta * pv.x, rv.y + beta * pv.y));
-        }
-        if (!S.flush) continue;
-        const int npend = S.npend;
-        const int iter0 = S.slot;  // position of the current iteration in its window
-        double2 rw[kLagMax];
-#pragma unroll
-        for (int t = 0; t < kLagMax; ++t) {
-            if (t >= npend) break;
-            const int pos_next = t + 1;  // window position of r_{i+1}
-            if (pos_next == iter0 + 1)
-                rw[t] = rv;
-            else if (pos_next == iter0)
-                rw[t] = r0;
-            else
-                rw[t] = to_d2(ring[(size_t)(pos_next % L) * st.ring_stride + i]);
-        }
-        const double* was = w_as + rh * wsz;
-        const double* wbs = w_bs + rh * wsz;
-        const double* wzn = w_zn + rh * wsz;
-        const int* wact = w_act + rh * wsz;
-        constexpr int G = 4;
-        for (int g0 = 0; g0 < S.nact; g0 += G) {
-            double2 pk[G], xk[G];
-#pragma unroll
-            for (int jq = 0; jq < G; ++jq)
-                if (g0 + jq < S.nact) {
-                    const int k = S.list[g0 + jq];
-                    pk[jq] = to_d2(ps.at<V>(k)[i]);
-                    xk[jq] = x.at<double2>(k)[i];
+                for (int u = 0; u < kItems; ++u) {
+                    const int it = it0 + u * stride;
+                    const int c = it >> lgSB, site = tl.cb0 + (it & (SB - 1));
+                    on[u] = it < nitem && site < I.g.vh;
+                    idx[u] = off + (size_t)c * I.g.vh + site;
+                    if (on[u]) {
+                        r0[u] = r_in[idx[u]];
+                        a[u] = Ap[idx[u]];
+                        pv[u] = p[idx[u]];
+                        if (S.base_on) xv[u] = x.at<double2>(base)[idx[u]];
+                    }
                 }
+#pragma unroll
+                for (int u = 0; u < kItems; ++u) {
+                    if (!on[u]) continue;
+                    double2 rv = to_d2(r0[u]);
+                    const double2 av = to_d2(a[u]), pd = to_d2(pv[u]);
+                    rv.x -= alpha * av.x;
+                    rv.y -= alpha * av.y;
+                    const V rl = from_d2<V>(rv);
+                    r_out[idx[u]] = rl;
+                    rv = to_d2(rl);
+                    acc[0] += rv.x * rv.x + rv.y * rv.y;
+                    if (S.base_on)
+                        x.at<double2>(base)[idx[u]] = make_double2(xv[u].x + alpha * pd.x, xv[u].y + alpha * pd.y);
+                    p[idx[u]] = from_d2<V>(make_double2(rv.x + beta * pd.x, rv.y + beta * pd.y));
+                }
+            }
+        }
+        // the shifted systems at the end of their window (residuals of the window
+        // are in the ring: a lane reads back the ones that it wrote above)
+        const int nact = S.flush ? S.nact : 0, npend = S.npend;
+        const double* w_as = w_tab + sy * 3 * kWinTab;
+        const double* w_bs = w_as + kWinTab;
+        const double* w_zn = w_bs + kWinTab;
+        const int* act = w_act + sy * kWinTab;
+        for (int it = first; nact > 0 && it < nitem; it += stride) {
+            const int c = it >> lgSB, site = tl.cb0 + (it & (SB - 1));
+            if (site >= I.g.vh) continue;
+            const size_t i = off + (size_t)c * I.g.vh + site;
+            double2 rw[kLagMax];
 #pragma unroll
             for (int t = 0; t < kLagMax; ++t) {
                 if (t >= npend) break;
+                rw[t] = to_d2(ring[(size_t)((t + 1) % L) * st.ring_stride + i]);
+            }
+            constexpr int G = 4;
+            for (int g0 = 0; g0 < nact; g0 += G) {
+                double2 pk[G], xk[G];
 #pragma unroll
                 for (int jq = 0; jq < G; ++jq)
-                    if (g0 + jq < S.nact) {
+                    if (g0 + jq < nact) {
                         const int k = S.list[g0 + jq];
-                        if (wact[t * n + k]) {
-                            const double aq = was[t * n + k], bq = wbs[t * n + k], zq = wzn[t * n + k];
-                            xk[jq] = make_double2(xk[jq].x + aq * pk[jq].x, xk[jq].y + aq * pk[jq].y);
-                            pk[jq] = to_d2(from_d2<V>(make_double2(zq * rw[t].x + bq * pk[jq].x,
-                                                                   zq * rw[t].y + bq * pk[jq].y)));
+                        pk[jq] = to_d2(ps.at<V>(k)[i]);
+                        xk[jq] = x.at<double2>(k)[i];
+                    }
+#pragma unroll
+                for (int t = 0; t < kLagMax; ++t) {
+                    if (t >= npend) break;
+#pragma unroll
+                    for (int jq = 0; jq < G; ++jq)
+                        if (g0 + jq < nact) {
+                            const int k = S.list[g0 + jq];
+                            if (act[t * n + k]) {
+                                const double aq = w_as[t * n + k], bq = w_bs[t * n + k], zq = w_zn[t * n + k];
+                                xk[jq] = make_double2(xk[jq].x + aq * pk[jq].x, xk[jq].y + aq * pk[jq].y);
+                                pk[jq] = to_d2(from_d2<V>(make_double2(zq * rw[t].x + bq * pk[jq].x,
+                                                                       zq * rw[t].y + bq * pk[jq].y)));
+                            }
                         }
+                }
+#pragma unroll
+                for (int jq = 0; jq < G; ++jq)
+                    if (g0 + jq < nact) {
+                        const int k = S.list[g0 + jq];
+                        x.at<double2>(k)[i] = xk[jq];
+                        ps.at<V>(k)[i] = from_d2<V>(pk[jq]);
                     }
             }
-#pragma unroll
-            for (int jq = 0; jq < G; ++jq)
-                if (g0 + jq < S.nact) {
-                    const int k = S.list[g0 + jq];
-                    x.at<double2>(k)[i] = xk[jq];
-                    ps.at<V>(k)[i] = from_d2<V>(pk[jq]);
-                }
         }
     }
-    block_sum<kMaxRhs>(acc, lds);
-    if (threadIdx.x == 0)
-        for (int q = 0; q < kMaxRhs; ++q) qout[(size_t)blockIdx.x * kMaxRhs + q] = acc[q];
+    wave_sum<1>(acc);
+    if (lane == 0) lds[wave] = acc[0];
+    __syncthreads();
+    if ((int)threadIdx.x < R) {
+        double v = 0.0;
+        for (int w = 0; w < nw; ++w) v += lds[threadIdx.x * nw + w];
+        qout[(size_t)blockIdx.x * kMaxRhs + threadIdx.x] = v;
+    }
 }
 
 // one block per system: its (tile, rhs) partials over the instance's tiles
@@ -786,7 +848,7 @@ __global__ void k_timestamp(unsigned long long* t) {
 template <class V>
 void launch_bdslash(const BatchDev& bd, int tps, const void* links, const V* in, V* out, int out_par,
                     const int* inst_done, hipStream_t s) {
-    bdslash_tps<V>(bd, tps, (const V*)links, in, out_par, BEpiStore<V>{out}, inst_done, s);
+    bdslash_tps<V>(bd, tps, (const V*)links, in, out_par, BEpiStore<V>{nullptr, out}, inst_done, s);
 }
 template void launch_bdslash<double2>(const BatchDev&, int, const void*, const double2*, double2*, int, const int*,
                                       hipStream_t);
@@ -796,7 +858,7 @@ template void launch_bdslash<float2>(const BatchDev&, int, const void*, const fl
 template <class V>
 void launch_bdslash_cg(const BatchDev& bd, int tps, const void* links, const V* w_o, const V* p, const V* r, V* Ap,
                        BState st, const int* inst_done, double* dpart, hipStream_t s) {
-    bdslash_tps<V>(bd, tps, (const V*)links, w_o, 0, BEpiCG<V>{Ap, p, r, st.sigma0_term, dpart}, inst_done, s);
+    bdslash_tps<V>(bd, tps, (const V*)links, w_o, 0, BEpiCG<V>{dpart, Ap, p, r, st.sigma0_term}, inst_done, s);
 }
 template void launch_bdslash_cg<double2>(const BatchDev&, int, const void*, const double2*, const double2*,
                                          const double2*, double2*, BState, const int*, double*, hipStream_t);
@@ -805,7 +867,7 @@ template void launch_bdslash_cg<float2>(const BatchDev&, int, const void*, const
 
 void launch_bdslash_resid(const BatchDev& bd, int tps, const double2* links, const double2* w_o, const double2* x,
                           const double2* b, double pole, double* part, double2* rout, hipStream_t s) {
-    bdslash_tps<double2>(bd, tps, links, w_o, 0, BEpiResid{x, b, rout, pole, part}, nullptr, s);
+    bdslash_tps<double2>(bd, tps, links, w_o, 0, BEpiResid{part, x, b, rout, pole}, nullptr, s);
 }
 
 template <class V>
@@ -823,8 +885,7 @@ void launch_bms_step(const BatchDev& bd, V* r, const V* Ap, V* p, VecPtrs x, Vec
                      const double* dpart, const double* qin, double* qout, int par, hipStream_t s) {
     (void)dpart;
     (void)qin;
-    const size_t lds = (size_t)kMaxRhs * st.lag * st.n * (3 * sizeof(double) + sizeof(int));
-    k_bms_step<V><<<bd.ntiles, kBlock, lds, s>>>(bd, r, Ap, p, x, ps, st, qout, par);
+    k_bms_step<V><<<bd.ntiles, kBlock, 0, s>>>(bd, r, Ap, p, x, ps, st, st.scal, st.w_tab, st.w_act, qout, par);
 }
 template void launch_bms_step<double2>(const BatchDev&, double2*, const double2*, double2*, VecPtrs, VecPtrs, BState,
                                        const double*, const double*, double*, int, hipStream_t);

@@ -33,7 +33,10 @@ struct stag_batch {
     std::vector<BTile> tiles_h;
     BInst* inst_d = nullptr;
     BTile* tiles_d = nullptr;
-    int tps = 2;
+    // 4: the fastest or within 2% of it over 4 to 27 lattices of 4^4 to 16^3x8 and
+    // 1 to 4 right-hand sides (9 lattices, 4 sources, whole solve: 7.7, 6.6, 5.9 and
+    // 7.8 ms for 1, 2, 4 and 8; autotune measures the handle's own)
+    int tps = 4;
     int link_nt = -1;            // links loaded non-temporally: -1 by field size, 0 no, 1 yes (tuned)
     int link12 = 0;              // operators read 12 reals per link (rows 0-1, row 2 rebuilt)
     int lag = 8;                 // shift-update window (divides the 16-iteration chunk)
@@ -111,7 +114,9 @@ stag_status build_tiles(stag_batch* c) {
         BInst& I = c->inst_h[i];
         I.tile0 = (int)c->tiles_h.size();
         I.ntiles = (I.g.vh + sb - 1) / sb;
-        for (int t = 0; t < I.ntiles; ++t) c->tiles_h.push_back(BTile{i, t * sb});
+        // blocks go round-robin over the XCDs: give the blocks of an XCD tiles
+        // that are neighbours in this lattice
+        for (int t = 0; t < I.ntiles; ++t) c->tiles_h.push_back(BTile{i, xcd_tile_slab(t, I.ntiles, I.g, sb) * sb});
     }
     const int nt = (int)c->tiles_h.size();
     if (nt > c->tiles_cap) {
@@ -425,7 +430,6 @@ stag_status stag_batch_create(stag_batch_handle* out, int n_inst, const int* dim
         (s = balloc(c, &st.inst_done, 2 * n_inst * sizeof(int))) ||
         (s = balloc(c, &st.t_done, (c->n_sys + 1) * sizeof(unsigned long long))) ||
         (s = balloc(c, &st.sigma0_term, n_inst * sizeof(double))) ||
-        (s = balloc(c, &st.hist, (size_t)c->n_sys * kLagMax * sizeof(MsHist))) ||
         (s = balloc(c, &st.scal, c->n_sys * sizeof(BScal))) ||
         (s = balloc(c, &st.w_tab, (size_t)c->n_sys * 3 * kWinTab * sizeof(double))) ||
         (s = balloc(c, &st.w_act, (size_t)c->n_sys * kWinTab * sizeof(int))) || (s = balloc(c, &c->sums, c->n_sys * sizeof(double))))
@@ -451,7 +455,7 @@ stag_status stag_batch_destroy(stag_batch_handle c) {
     if (c->s) hipStreamSynchronize(c->s);
     void* bufs[] = {c->inst_d, c->tiles_d, c->links64, c->links32, c->b, c->r, c->p, c->Ap, c->w, c->e, c->res,
                     c->pool_x, c->pool_p, c->st.it[0], c->st.it[1], c->st.fin, c->st.sys_done, c->st.inst_done,
-                    c->st.t_done, c->st.sigma0_term, c->st.hist, c->st.scal, c->st.w_tab, c->st.w_act, c->dpart, c->qpart[0], c->qpart[1], c->gpart, c->sums};
+                    c->st.t_done, c->st.sigma0_term, c->st.scal, c->st.w_tab, c->st.w_act, c->dpart, c->qpart[0], c->qpart[1], c->gpart, c->sums};
     for (void* b : bufs)
         if (b) hipFree(b);
     for (auto& g : c->graphs)

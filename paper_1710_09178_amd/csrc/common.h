@@ -183,7 +183,7 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ part, 
 // Blocks are dispatched round-robin over the 8 XCDs; remap so each XCD works
 // on one contiguous range of tiles (neighbouring sites share its L2).  The map
 // is a permutation of [0, nb) for any nb.
-__device__ __forceinline__ int xcd_tile(int b, int nb) {
+__host__ __device__ __forceinline__ int xcd_tile(int b, int nb) {
     const int nx = 8;
     const int q = nb / nx, r = nb % nx;
     const int xcd = b % nx, k = b / nx;
@@ -198,7 +198,7 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
 // of the lattice (t-slices, the contiguous ranges, would put both t faces of
 // every slice there).  Otherwise the contiguous-range map above.  A
 // permutation of [0, nb).
-__device__ __forceinline__ int xcd_tile_slab(int b, int nb, const Geom& g, int SB) {
+__host__ __device__ __forceinline__ int xcd_tile_slab(int b, int nb, const Geom& g, int SB) {
     const int plane = g.nx * g.ny / 2;  // half-lattice sites of one (z, t) plane
     int NZ = 0, W = 0;                  // tile rows along z, tiles per row
     if (plane % SB == 0) {
