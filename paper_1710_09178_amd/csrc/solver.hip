@@ -237,16 +237,17 @@ void store_graph(stag_ctx* c, const ChunkKey& key, hipGraphExec_t exec) {
 }
 
 // Enqueue iterations in chunks and poll the device "done" flag once per chunk,
-// keeping two chunks in flight.  between_chunks(par_next) may enqueue extra
-// work after every chunk (reliable updates); it receives the parity of the
-// next iteration.  Without extra work or profiling, a chunk is captured once
-// into a hipGraph (kernel nodes only) and replayed: the chunk length is a
-// multiple of 2 and of the window, so every chunk repeats the same launches.
+// keeping two chunks in flight.  With every > 0, between(par_next) enqueues
+// extra work after each `every` iterations (reliable updates); it receives the
+// parity of the next iteration.  Without extra work or profiling, a chunk is
+// captured once into a hipGraph (kernel nodes only) and replayed: the chunk
+// length is a multiple of 2 and of the window, so every chunk repeats the same
+// launches.
 // Issue chunks into the two flag slots in turn and wait for them in order:
-// up to two in flight (one with two_in_flight false, and one once
-// past_estimate() holds), until a chunk's flag says the solve has stopped.
+// up to two in flight (one once past_estimate() holds), until a chunk's flag
+// says the solve has stopped.
 template <class Issue, class Past>
-stag_status drive_chunks(stag_ctx* c, Issue& issue_chunk, bool two_in_flight, Past past_estimate) {
+stag_status drive_chunks(stag_ctx* c, Issue& issue_chunk, Past past_estimate) {
     int q[2], nq = 0, next_slot = 0;
     auto issue = [&]() {
         issue_chunk(next_slot);
@@ -254,14 +255,14 @@ stag_status drive_chunks(stag_ctx* c, Issue& issue_chunk, bool two_in_flight, Pa
         next_slot ^= 1;
     };
     issue();
-    if (two_in_flight && !past_estimate()) issue();
+    if (!past_estimate()) issue();
     for (;;) {
         const int s0 = q[0];
         q[0] = q[1];
         --nq;
         HIP_OR_FAIL(c, hipEventSynchronize(c->chunk_ev[s0]));
         if (c->done_host[s0]) break;
-        const int cap = (!two_in_flight || past_estimate()) ? 1 : 2;
+        const int cap = past_estimate() ? 1 : 2;
         while (nq < cap) issue();
     }
     HIP_OR_FAIL(c, hipGetLastError());
@@ -281,8 +282,7 @@ inline int small_chunk(int chunk, int L) {
 
 template <class V, class Between>
 stag_status run_iterations(stag_ctx* c, const LinkSet& ls, const Krylov<V>& K, VecPtrs X, VecPtrs P, int chunk,
-                           EvRec& rec, Between between_chunks, bool two_in_flight = true,
-                           bool extra_work = false, int pred = 0) {
+                           EvRec& rec, Between between, int every = 0, int pred = 0) {
     const Geom& g = c->g;
     const double mt = c->st_host->mass_term;
     const int L = c->st_host->lag;
@@ -322,7 +322,7 @@ stag_status run_iterations(stag_ctx* c, const LinkSet& ls, const Krylov<V>& K, V
             prof_end(c, a, 2, rec);
         }
     };
-    const bool graphs = c->use_graph && !c->prof_on && !extra_work && chunk % 2 == 0 && chunk % L == 0;
+    const bool graphs = c->use_graph && !c->prof_on && !every && chunk % 2 == 0 && chunk % L == 0;
     // one captured graph per chunk length; every replay starts at a multiple
     // of 2 and of L, like the capture
     auto graph_for = [&](int len, hipGraphExec_t& exec) -> stag_status {
@@ -372,7 +372,12 @@ stag_status run_iterations(stag_ctx* c, const LinkSet& ls, const Krylov<V>& K, V
     if (pred > 0 && small < chunk && (e = graph_for(small, exec_small))) return e;
     auto issue_chunk = [&](int slot) {
         // the launch of device iteration pred (the expected stop) sets the flag
-        const int len = (pred > 0 && it_issued + chunk > pred + 1) ? small : chunk;
+        int len = (pred > 0 && it_issued + chunk > pred + 1) ? small : chunk;
+        if (every > 0) {
+            // to the expected stop, then in short steps; never past an update
+            len = pred > it_issued ? pred + 1 - it_issued : chunk;
+            len = std::min(len, every - it_issued % every);
+        }
         hipGraphExec_t ex = len == chunk ? exec : exec_small;
         if (ex) {
             hipGraphLaunch(ex, c->s);
@@ -380,12 +385,12 @@ stag_status run_iterations(stag_ctx* c, const LinkSet& ls, const Krylov<V>& K, V
         } else {
             enqueue_chunk(len);
         }
-        between_chunks(it_issued & 1);
+        if (every > 0 && it_issued % every == 0) between(it_issued & 1);
         // the flag the next iteration would read
         hipMemcpyAsync(&c->done_host[slot], &c->st->done[it_issued & 1], sizeof(int), hipMemcpyDeviceToHost, c->s);
         hipEventRecord(c->chunk_ev[slot], c->s);
     };
-    return drive_chunks(c, issue_chunk, two_in_flight, [&]() { return pred > 0 && it_issued > pred; });
+    return drive_chunks(c, issue_chunk, [&]() { return pred > 0 && it_issued > pred; });
 }
 
 // The fused loop (FP64 or FP32 Krylov vectors, window L >= 2): iteration j is
@@ -528,7 +533,7 @@ stag_status run_fused(stag_ctx* c, const LinkSet& ls, const Krylov<V>& K, VecPtr
         hipMemcpyAsync(&c->done_host[slot], &c->st->done[it_issued & 1], sizeof(int), hipMemcpyDeviceToHost, c->s);
         hipEventRecord(c->chunk_ev[slot], c->s);
     };
-    if ((e = drive_chunks(c, issue_chunk, true, [&]() { return pred > 0 && it_issued > pred + 1; }))) return e;
+    if ((e = drive_chunks(c, issue_chunk, [&]() { return pred > 0 && it_issued > pred + 1; }))) return e;
     if (nsh > 0) launch_ms_flush(g, (const V*)K.r, X, P, c->st, nullptr, n, base, L, true, rows, c->s);
     HIP_OR_FAIL(c, hipGetLastError());
     return STAG_OK;
@@ -651,7 +656,7 @@ stag_status ms_solve_t(stag_ctx* c, const LinkSet& ls, double mass, const stag_r
         if (fused)
             e = run_fused<V>(c, ls, K, X, P, c->chunk, rec, pred);
         else
-            e = run_iterations<V>(c, ls, K, X, P, c->chunk, rec, [](int) {}, true, false, pred);
+            e = run_iterations<V>(c, ls, K, X, P, c->chunk, rec, [](int) {}, 0, pred);
         if (e) return e;
         HIP_OR_FAIL(c, hipMemcpyAsync(h, c->st, sizeof(MsState), hipMemcpyDeviceToHost, c->s));
         HIP_OR_FAIL(c, hipStreamSynchronize(c->s));
@@ -685,9 +690,13 @@ void true_residuals(stag_ctx* c, const LinkSet& ls, double mass, const stag_rati
 // CG in FP32 on (A + pole) for one pole, started from the FP64 residual of x
 // (FP64), whose residual is recomputed in FP64 every `every` iterations and
 // copied into the FP32 Krylov residual (reliable update; the search direction
-// is kept).  Returns the iterations run.
+// is kept).  Returns the iterations run.  pred: in, the iterations to expect (0:
+// unknown), and out, those of the last CG; a pole takes about as many as its
+// neighbour, and the launches queued behind the stop (2-3 us each, a chunk of
+// 50 iterations where 5 to 10 are enough) cost more than the solve.
+constexpr int kRefineChunk = 4;  // iterations between polls where none are expected
 stag_status refine_pole(stag_ctx* c, const LinkSet& ls, double mass, double pole, double tol, int maxiter,
-                        const double2* b, double2* x, double bb, int every, int& iters_out, bool& converged) {
+                        const double2* b, double2* x, double bb, int every, int& pred, int& iters_out, bool& converged) {
     const Geom& g = c->g;
     const int nbr = dslash_grid(g, c->tps);
     const int nq = ms_update_grid(g);
@@ -728,19 +737,19 @@ stag_status refine_pole(stag_ctx* c, const LinkSet& ls, double mass, double pole
             if (!ok) continue;  // (a wait timed out) start again from the residual of what x holds
         } else {
             e = run_iterations<float2>(
-                c, ls, K, X, P, every, rec, [&](int par_next) { reliable(c->qpart[par_next]); }, false, true);
+                c, ls, K, X, P, kRefineChunk, rec, [&](int par_next) { reliable(c->qpart[par_next]); }, every, pred);
             if (e) return e;
             HIP_OR_FAIL(c, hipMemcpyAsync(h, c->st, sizeof(MsState), hipMemcpyDeviceToHost, c->s));
-            HIP_OR_FAIL(c, hipStreamSynchronize(c->s));
         }
-        iters_out += h->fin.iter;
-        if (h->fin.nonfinite) return fail(c, STAG_ERR_NONFINITE, "non-finite value in the refinement CG");
         // the step kernel may have stopped on a recursive residual: check in FP64
         launch_dslash(g, ls, x, c->tmp_o, 1, c->tps, nullptr, c->s);
         launch_dslash_resid(g, ls, c->tmp_o, x, b, coef, c->gpart, c->tps, c->s);
         launch_finalize(c->gpart, nbr, 1, c->scal, c->s);
         HIP_OR_FAIL(c, hipMemcpyAsync(c->scal_host, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->s));
         HIP_OR_FAIL(c, hipStreamSynchronize(c->s));
+        iters_out += h->fin.iter;
+        pred = h->fin.iter;
+        if (h->fin.nonfinite) return fail(c, STAG_ERR_NONFINITE, "non-finite value in the refinement CG");
         if (c->scal_host[0] <= tol * tol * bb) {
             converged = true;
             break;
@@ -827,11 +836,12 @@ stag_status ms_solve_mixed(stag_ctx* c, double mass, const stag_rational* r, dou
         // violate for light poles.
         LinkSet lr;
         if ((e = get_links(c, STAG_LINKS_F32_18, lr))) return e;
+        int pred = 0;
         for (int k = 0; k < r->n; ++k) {
             int it = 0;
             bool conv = false;
             if ((e = refine_pole(c, lr, mass, r->pole[k], tol, std::max(1, maxiter - res.iters), b, x[k], r1.bb,
-                                 std::max(1, opts->reliable_every), it, conv)))
+                                 std::max(1, opts->reliable_every), pred, it, conv)))
                 return e;
             ipp[k] += it;
             res.iters += it;
