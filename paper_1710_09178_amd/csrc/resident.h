@@ -33,7 +33,8 @@ struct ResidentArgs {
 };
 
 // Can this lattice and operator run in one co-resident grid on the current device?
-bool resident_fits(const Geom& g, const LinkSet& ls, bool fp64);
+// (refine: the FP32 CG of a single system, continued from given vectors)
+bool resident_fits(const Geom& g, const LinkSet& ls, bool fp64, bool refine = false);
 // Fills the exchange area and enqueues the solver; V = double2 (operator
 // format fmt64) or float2 (format fmt32).
 template <class V>

@@ -245,13 +245,25 @@ struct ResStep {  // scalars of one shift in one step; a frozen shift has {0, 1,
 // (16^3x8, 12-real links: 21.3 against 19.1 us).  Both hops of a direction in
 // one lane, with four waves, take 8.0 us per iteration where this takes 7.0
 // (16^3x8, 20 poles).
+//
+// FP32 leaves the registers of a second block per CU, and with it lattices of up
+// to 512 tiles: 128 are enough for the single system of a refinement (SHIFTS
+// false: no window, no ring), while the window's code spills 69, outside the
+// wait for w.  Mixed solve of 12 poles, one launch per solve against the loops:
+// 20^3x8 5.3 against 8.1 ms, 16^3x12 6.7 against 10.2 ms, 16^3x8 4.1 against
+// 8.0 ms.  A third block per CU (80 registers, 90 spilled) takes 18.8 us per
+// iteration where the loop takes 22 (24^3x6), and 15% more than two on the
+// lattices that two hold: not used.
 template <class Link>
-__global__ __launch_bounds__(kResThreads, 2) void k_resident(Geom g, Link L, ResidentArgs<typename Link::C> a) {
+constexpr int kResWaves = sizeof(typename Link::C) == sizeof(float2) ? 4 : 2;  // per SIMD
+template <class Link, bool SHIFTS>
+__global__ __launch_bounds__(kResThreads, kResWaves<Link>) void k_resident(Geom g, Link L,
+                                                                           ResidentArgs<typename Link::C> a) {
     using C = typename Link::C;
     using R = typename Link::R;
     using X = XElem<C>;
     constexpr int SB = kResTile, NW = kResThreads / 64;
-    __shared__ C ring[2][kLagMax][3 * SB];
+    __shared__ C ring[SHIFTS ? 2 : 1][SHIFTS ? kLagMax : 1][3 * SB];
     __shared__ C wl[3 * SB], al[3 * SB];
     __shared__ double red[4][4 * NW];
     __shared__ double2* xs[kMaxPoles];
@@ -471,7 +483,7 @@ __global__ __launch_bounds__(kResThreads, 2) void k_resident(Geom g, Link L, Res
     double alpha = 0.0, beta = 0.0;
     for (int step = 0;; ++step) {
         // (the group of shifts applied below: its loads run beside the hops)
-        const bool one = todo > 0 && elem;
+        const bool one = SHIFTS && todo > 0 && elem;
         if (one) flush_load(buf ^ 1, todo_first, (todo - 1) * G);
         // ---- w = D_oe p
         const unsigned wv = xw + (step & 1) * vb;
@@ -494,8 +506,8 @@ __global__ __launch_bounds__(kResThreads, 2) void k_resident(Geom g, Link L, Res
                     bs = beta * q * q;
                     zr = zn;
                 }
-                if (lane < n) hist[(buf * lag + pend) * n + lane] = ResStep{as, bs, zr};
-                if (pend == 0) {
+                if (SHIFTS && lane < n) hist[(buf * lag + pend) * n + lane] = ResStep{as, bs, zr};
+                if (SHIFTS && pend == 0) {
                     const int mine = lane < n && lane != base && (active || first);
                     const u64 m = __ballot(mine != 0);
                     if (mine) list[buf][__popcll(m & ((1ull << lane) - 1ull))] = lane;
@@ -506,7 +518,7 @@ __global__ __launch_bounds__(kResThreads, 2) void k_resident(Geom g, Link L, Res
                 alpha_old = alpha;
                 beta_old = beta;
             }
-            ++pend;
+            if (SHIFTS) ++pend;
         }
         lds_barrier();
         ask(wv, n0);
@@ -524,12 +536,12 @@ __global__ __launch_bounds__(kResThreads, 2) void k_resident(Geom g, Link L, Res
         }
         if (one) flush_apply(buf ^ 1, lag, (todo - 1) * G);
         if (todo > 0) --todo;
-        for (int k = 1; k < per && todo > 0; ++k, --todo)
+        for (int k = 1; SHIFTS && k < per && todo > 0; ++k, --todo)
             if (elem) {
                 flush_load(buf ^ 1, todo_first, (todo - 1) * G);
                 flush_apply(buf ^ 1, lag, (todo - 1) * G);
             }
-        if (pend == lag) {  // a window is full; the one before it is done (lag iterations, per groups each)
+        if (SHIFTS && pend == lag) {  // a window is full; the one before it is done (lag iterations, per groups each)
             todo = (shifts_of(buf) + G - 1) / G;
             per = (todo + lag - 1) / lag;
             todo_first = first;
@@ -624,12 +636,12 @@ __global__ __launch_bounds__(kResThreads, 2) void k_resident(Geom g, Link L, Res
         if (sh_base_on) o_x = make_double2(fma(alpha, pd.x, o_x.x), fma(alpha, pd.y, o_x.y));
         o_r = cg_r_next(o_r, o_a, alpha);
         o_p = cg_p_next(o_r, o_p, beta);
-        if (own) ring[buf][pend][oo] = o_r;
+        if (SHIFTS && own) ring[buf][pend][oo] = o_r;
         if (step + 1 == a.max_steps) break;
     }
     // ---- the rest of the finished window, the steps of the last one, the results
     lds_barrier();  // (the ring, for the other lane of an element)
-    if (elem) {
+    if (SHIFTS && elem) {
         for (; todo > 0; --todo) {
             flush_load(buf ^ 1, todo_first, (todo - 1) * G);
             flush_apply(buf ^ 1, lag, (todo - 1) * G);
@@ -641,7 +653,7 @@ __global__ __launch_bounds__(kResThreads, 2) void k_resident(Geom g, Link L, Res
             }
     }
     if (own) {
-        if (first && pend == 0)  // stopped before the first step
+        if (SHIFTS && first && pend == 0)  // stopped before the first step
             for (int k = 0; k < n; ++k) xs[k][oi] = make_double2(0.0, 0.0);
         xs[base][oi] = o_x;
         if (!fresh) {
@@ -678,7 +690,7 @@ __global__ void k_fill_empty(u4v* __restrict__ p, size_t n) {
 // device; 0 where that is unknown).
 constexpr size_t kResHistMax = (size_t)2 * kLagMax * kMaxPoles * sizeof(ResStep);
 constexpr int kResDevices = 64;
-template <class Link>
+template <class Link, bool SHIFTS>
 int capacity() {
     static std::atomic<int> known[kResDevices];  // capacity + 1
     int dev = -1, blocks = 0, cus = 0, coop = 0;
@@ -687,8 +699,8 @@ int capacity() {
     if (k) return k - 1;
     if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, (const void*)k_resident<Link>, kResThreads,
-                                                     kResHistMax) != hipSuccess) {
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, (const void*)k_resident<Link, SHIFTS>,
+                                                     kResThreads, SHIFTS ? kResHistMax : 0) != hipSuccess) {
         (void)hipGetLastError();
         blocks = 0;
     }
@@ -712,19 +724,26 @@ void with_link(const LinkSet& ls, float2, Fn fn) {
         fn(LinkS18{ls.s18});
 }
 
+// Single systems that continue from given vectors (b = NULL) in FP32 have a
+// kernel of their own; others take the general one.
 template <class V>
+bool single(const ResidentArgs<V>& a) {
+    return sizeof(V) == sizeof(float2) && a.n == 1 && !a.b;
+}
+template <bool SHIFTS, class V>
 bool fits(const Geom& g, const LinkSet& ls) {
     bool ok = false;
     const int nb = resident_blocks(g);
-    with_link(ls, V{}, [&](auto L) { ok = nb <= kResMax && nb <= capacity<decltype(L)>(); });
+    with_link(ls, V{}, [&](auto L) { ok = nb <= kResMax && nb <= capacity<decltype(L), SHIFTS>(); });
     return ok;
 }
 
 }  // namespace
 
-bool resident_fits(const Geom& g, const LinkSet& ls, bool fp64) {
+bool resident_fits(const Geom& g, const LinkSet& ls, bool fp64, bool refine) {
     if (ls.naik) return false;
-    return fp64 ? fits<double2>(g, ls) : fits<float2>(g, ls);
+    if (refine) return fits<false, float2>(g, ls);
+    return fp64 ? fits<true, double2>(g, ls) : fits<true, float2>(g, ls);
 }
 
 template <class V>
@@ -736,8 +755,14 @@ hipError_t launch_resident(const Geom& g, const LinkSet& ls, const ResidentArgs<
         Geom gg = g;
         ResidentArgs<V> aa = a;
         void* args[] = {&gg, &L, &aa};
-        err = hipLaunchCooperativeKernel((const void*)k_resident<decltype(L)>, dim3(resident_blocks(g)),
-                                         dim3(kResThreads), args, (size_t)2 * a.lag * a.n * sizeof(ResStep), s);
+        const void* kernel = (const void*)k_resident<decltype(L), true>;
+        size_t dyn = (size_t)2 * a.lag * a.n * sizeof(ResStep);
+        if constexpr (sizeof(V) == sizeof(float2))
+            if (single(a)) {
+                kernel = (const void*)k_resident<decltype(L), false>;
+                dyn = 0;
+            }
+        err = hipLaunchCooperativeKernel(kernel, dim3(resident_blocks(g)), dim3(kResThreads), args, dyn, s);
     });
     return err;
 }

@@ -606,8 +606,8 @@ bool ensure_exchange(stag_ctx* c) {
 // Is the resident solver the one to use?  On the lattices it holds a CG
 // iteration takes 4-7 us where the fused loop takes 12-14 us (8^4: 5.2 against
 // 11.9 us, 16^3x8: 7.2 against 14.1 us, 12 poles, whole solve over iterations).
-bool resident_ready(stag_ctx* c, const LinkSet& ls, bool fp64) {
-    return c->fused == 1 && c->lag >= 2 && c->resident && !c->prof_on && resident_fits(c->g, ls, fp64) &&
+bool resident_ready(stag_ctx* c, const LinkSet& ls, bool fp64, bool refine = false) {
+    return c->fused == 1 && c->lag >= 2 && c->resident && !c->prof_on && resident_fits(c->g, ls, fp64, refine) &&
            ensure_exchange(c);
 }
 
@@ -717,7 +717,7 @@ stag_status refine_pole(stag_ctx* c, const LinkSet& ls, double mass, double pole
         int base;
         const double one = 1.0;
         init_state(h, 1, &pole, &one, 0.0, mass, tol, maxiter - iters_out, base);
-        const bool resident = resident_ready(c, ls, false);
+        const bool resident = resident_ready(c, ls, false, true);
         if (resident) h->lag = 2;  // (no shifts: the window only sizes buffers)
         h->bb_given = 1;
         h->it[0].bb = bb;
