@@ -63,19 +63,12 @@ stag_status check_common(stag_ctx* c, bool need_gauge) {
     return STAG_OK;
 }
 
-// order the internal stream after the caller's stream
-stag_status enter(stag_ctx* c) {
-    HIP_OR_FAIL(c, hipSetDevice(c->device));
-    HIP_OR_FAIL(c, hipEventRecord(c->ev_in, c->user));
-    HIP_OR_FAIL(c, hipStreamWaitEvent(c->s, c->ev_in, 0));
-    return STAG_OK;
-}
-
 // order the caller's stream after the internal stream
 stag_status leave(stag_ctx* c) {
     HIP_OR_FAIL(c, hipGetLastError());
     HIP_OR_FAIL(c, hipEventRecord(c->ev_out, c->s));
     HIP_OR_FAIL(c, hipStreamWaitEvent(c->user, c->ev_out, 0));
+    c->inside = false;
     return STAG_OK;
 }
 
@@ -307,6 +300,7 @@ stag_status stag_create(stag_handle* out, const int dims[4], void* hip_stream) {
 
 stag_status stag_destroy(stag_handle c) {
     if (!c) return STAG_OK;
+    // (work of the handle on the caller's stream ends before hipFree returns)
     if (c->s) hipStreamSynchronize(c->s);
     void* bufs[] = {c->links_d12, c->links_s18, c->links_h12, c->long_d18, c->long_d12, c->long_s18, c->long_h12,
                     c->naik_w3, c->r32, c->p32, c->p2_32, c->Ap32, c->w32,
@@ -347,20 +341,22 @@ stag_status stag_set_gauge(stag_handle c, const double* U) {
     stag_status e = check_common(c, false);
     if (e) return e;
     if (!aligned16(U)) return fail(c, STAG_ERR_INVALID_ARG, "gauge pointer is NULL or not 16-byte aligned");
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     launch_gauge_to_internal(c->g, (const double2*)U, c->links, c->s);
     links_changed(c);
     c->has_gauge = true;
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_get_gauge(stag_handle c, double* U) {
     stag_status e = check_common(c, true);
     if (e) return e;
     if (!aligned16(U)) return fail(c, STAG_ERR_INVALID_ARG, "gauge pointer is NULL or not 16-byte aligned");
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     launch_gauge_to_canon(c->g, c->links, (double2*)U, c->s);
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_vec_import(stag_handle c, void* out, const double* in, int parity) {
@@ -369,9 +365,10 @@ stag_status stag_vec_import(stag_handle c, void* out, const double* in, int pari
     if (!aligned16(out) || !aligned16(in)) return fail(c, STAG_ERR_INVALID_ARG, "vector pointer NULL or misaligned");
     if (parity != 0 && parity != 1) return fail(c, STAG_ERR_INVALID_ARG, "parity must be 0 or 1");
     if (out == (const void*)in) return fail(c, STAG_ERR_INVALID_ARG, "in and out must differ");
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     launch_vec_to_internal(c->g, (const double2*)in, (double2*)out, c->s);
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_vec_export(stag_handle c, double* out, const void* in, int parity) {
@@ -380,9 +377,10 @@ stag_status stag_vec_export(stag_handle c, double* out, const void* in, int pari
     if (!aligned16(out) || !aligned16(in)) return fail(c, STAG_ERR_INVALID_ARG, "vector pointer NULL or misaligned");
     if (parity != 0 && parity != 1) return fail(c, STAG_ERR_INVALID_ARG, "parity must be 0 or 1");
     if ((const void*)out == in) return fail(c, STAG_ERR_INVALID_ARG, "in and out must differ");
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     launch_vec_to_canon(c->g, (const double2*)in, (double2*)out, c->s);
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_mom_import(stag_handle c, void* out, const double* in) {
@@ -390,9 +388,10 @@ stag_status stag_mom_import(stag_handle c, void* out, const double* in) {
     if (e) return e;
     if (!aligned16(out) || !aligned16(in) || out == (const void*)in)
         return fail(c, STAG_ERR_INVALID_ARG, "momentum pointers NULL, misaligned or equal");
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     launch_mom_to_internal(c->g, in, (double*)out, 0, c->s);
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_mom_export(stag_handle c, double* out, const void* in) {
@@ -400,9 +399,10 @@ stag_status stag_mom_export(stag_handle c, double* out, const void* in) {
     if (e) return e;
     if (!aligned16(out) || !aligned16(in) || (const void*)out == in)
         return fail(c, STAG_ERR_INVALID_ARG, "momentum pointers NULL, misaligned or equal");
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     launch_mom_to_canon(c->g, (const double*)in, out, c->s);
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_dslash(stag_handle c, void* out, const void* in, int out_parity) {
@@ -411,7 +411,8 @@ stag_status stag_dslash(stag_handle c, void* out, const void* in, int out_parity
     if (!aligned16(out) || !aligned16(in) || out == in)
         return fail(c, STAG_ERR_INVALID_ARG, "vector pointers NULL, misaligned or equal");
     if (out_parity != 0 && out_parity != 1) return fail(c, STAG_ERR_INVALID_ARG, "parity must be 0 or 1");
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     LinkSet ls;
     if ((e = get_links(c, -1, ls))) return e;
     const bool timed = c->prof_on && c->prof_ev.size() >= 2;
@@ -427,7 +428,7 @@ stag_status stag_dslash(stag_handle c, void* out, const void* in, int out_parity
         c->prof_cnt[kind] += 1;
         c->prof_samples[kind].push_back(ms);
     }
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_mdagm(stag_handle c, void* out, const void* in, double mass) {
@@ -436,12 +437,13 @@ stag_status stag_mdagm(stag_handle c, void* out, const void* in, double mass) {
     if (!aligned16(out) || !aligned16(in) || out == in)
         return fail(c, STAG_ERR_INVALID_ARG, "vector pointers NULL, misaligned or equal");
     if (!std::isfinite(mass)) return fail(c, STAG_ERR_INVALID_ARG, "mass must be finite");
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     LinkSet ls;
     if ((e = get_links(c, -1, ls))) return e;
     launch_dslash(c->g, ls, (const double2*)in, c->tmp_o, 1, c->tps, nullptr, c->s);
     launch_dslash_axpy(c->g, ls, c->tmp_o, (const double2*)in, 4.0 * mass * mass, (double2*)out, c->tps, c->s);
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_power_estimate(stag_handle c, double mass, int iters, uint64_t seed, double* lam_out) {
@@ -449,7 +451,7 @@ stag_status stag_power_estimate(stag_handle c, double mass, int iters, uint64_t 
     if (e) return e;
     if (!std::isfinite(mass) || iters < 0 || !lam_out)
         return fail(c, STAG_ERR_INVALID_ARG, "need a finite mass, iters >= 0 and lam_out");
-    if ((e = enter(c))) return e;
+    if ((e = begin_internal(c))) return e;
     if ((e = power_rayleigh_impl(c, mass, iters, seed, lam_out))) return e;
     return leave(c);
 }
@@ -459,7 +461,7 @@ stag_status stag_check_spectrum(stag_handle c, double mass, double xmin, double 
     if (e) return e;
     if (!std::isfinite(mass) || !std::isfinite(xmin) || !std::isfinite(xmax) || !(xmin < xmax))
         return fail(c, STAG_ERR_INVALID_ARG, "need a finite mass and xmin < xmax");
-    if ((e = enter(c))) return e;
+    if ((e = begin_internal(c))) return e;
     const stag_status chk = spectrum_check_impl(c, mass, xmin, xmax, lam_out);
     if ((e = leave(c))) return e;
     return chk;
@@ -475,13 +477,14 @@ stag_status stag_dslash_sloppy(stag_handle c, void* out, const void* in, int out
     if (out_parity != 0 && out_parity != 1) return fail(c, STAG_ERR_INVALID_ARG, "parity must be 0 or 1");
     if (format != STAG_LINKS_F32_18 && format != STAG_LINKS_F16_12)
         return fail(c, STAG_ERR_INVALID_ARG, "sloppy format must be STAG_LINKS_F32_18 or STAG_LINKS_F16_12");
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     LinkSet ls;
     if ((e = get_links(c, format, ls)) || (e = ensure_fp32_workspace(c))) return e;
     launch_vec_narrow(c->g, (const double2*)in, c->p32, c->s);
     launch_dslash32(c->g, ls, c->p32, c->w32, out_parity, c->tps, nullptr, c->s);
     launch_vec_widen(c->g, c->w32, (double2*)out, c->s);
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_mdagm_sloppy(stag_handle c, void* out, const void* in, double mass, int format) {
@@ -492,14 +495,15 @@ stag_status stag_mdagm_sloppy(stag_handle c, void* out, const void* in, double m
     if (!std::isfinite(mass)) return fail(c, STAG_ERR_INVALID_ARG, "mass must be finite");
     if (format != STAG_LINKS_F32_18 && format != STAG_LINKS_F16_12)
         return fail(c, STAG_ERR_INVALID_ARG, "sloppy format must be STAG_LINKS_F32_18 or STAG_LINKS_F16_12");
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     LinkSet ls;
     if ((e = get_links(c, format, ls)) || (e = ensure_fp32_workspace(c))) return e;
     launch_vec_narrow(c->g, (const double2*)in, c->p32, c->s);
     launch_dslash32(c->g, ls, c->p32, c->w32, 1, c->tps, nullptr, c->s);
     launch_dslash32_axpy(c->g, ls, c->w32, c->p32, 4.0 * mass * mass, c->Ap32, c->tps, c->s);
     launch_vec_widen(c->g, c->Ap32, (double2*)out, c->s);
-    return leave(c);
+    return on.end();
 }
 
 namespace {
@@ -525,7 +529,7 @@ stag_status solve_entry(stag_handle c, double mass, const stag_rational* r, doub
         if (!(mixed->tol_sloppy > 0.0) || mixed->tol_sloppy >= 1.0 || mixed->reliable_every < 1)
             return fail(c, STAG_ERR_INVALID_ARG, "need 0 < tol_sloppy < 1 and reliable_every >= 1");
     }
-    if ((e = enter(c))) return e;
+    if ((e = begin_internal(c))) return e;
     if ((e = ensure_pool(c, r->n))) return e;
     std::vector<double2*> xs(r->n);
     for (int k = 0; k < r->n; ++k) xs[k] = x ? (double2*)x[k] : pool_vec(c->pool_x, c->g, k);
@@ -607,7 +611,7 @@ stag_status stag_fermion_action(stag_handle c, double mass, const stag_rational*
     if ((e = check_rational(c, r, mass))) return e;
     if (!(tol > 0.0) || maxiter < 1) return fail(c, STAG_ERR_INVALID_ARG, "need tol > 0 and maxiter >= 1");
     if (!aligned16(phi) || !S) return fail(c, STAG_ERR_INVALID_ARG, "phi NULL/misaligned or S_out NULL");
-    if ((e = enter(c))) return e;
+    if ((e = begin_internal(c))) return e;
     SolveResult res;
     if ((e = fermion_action_impl(c, mass, r, tol, maxiter, (const double2*)phi, S, res))) return e;
     if ((e = leave(c))) return e;
@@ -628,7 +632,7 @@ stag_status stag_fermion_force(stag_handle c, double mass, const stag_rational* 
     if (!(tol > 0.0) || maxiter < 1) return fail(c, STAG_ERR_INVALID_ARG, "need tol > 0 and maxiter >= 1");
     if (!aligned16(phi) || !aligned16(mom)) return fail(c, STAG_ERR_INVALID_ARG, "phi/mom NULL or misaligned");
     if (!std::isfinite(dt)) return fail(c, STAG_ERR_INVALID_ARG, "dt must be finite");
-    if ((e = enter(c))) return e;
+    if ((e = begin_internal(c))) return e;
     SolveResult res;
     if ((e = fermion_force_impl(c, mass, r, tol, maxiter, (const double2*)phi, (double*)mom, dt, res))) return e;
     if ((e = leave(c))) return e;
@@ -645,23 +649,26 @@ stag_status stag_gauge_force(stag_handle c, double beta, void* mom, double dt) {
     if (e) return e;
     if (!aligned16(mom) || !std::isfinite(beta) || !std::isfinite(dt))
         return fail(c, STAG_ERR_INVALID_ARG, "mom NULL/misaligned or beta/dt not finite");
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     launch_gauge_force(c->g, c->links, beta, (double*)mom, dt, c->s);
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_gauge_action(stag_handle c, double beta, double* S, double* plaq) {
     stag_status e = check_common(c, true);
     if (e) return e;
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     if ((e = gauge_action_impl(c, beta, S, plaq))) return e;
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_polyakov_loop(stag_handle c, double* re, double* im) {
     stag_status e = check_common(c, true);
     if (e) return e;
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     const int nb = launch_polyakov(c->g, c->links, c->gpart, c->s);
     launch_finalize(c->gpart, nb, 2, c->scal, c->s);
     HIP_OR_FAIL(c, hipMemcpyAsync(c->scal_host, c->scal, 2 * sizeof(double), hipMemcpyDeviceToHost, c->s));
@@ -669,7 +676,7 @@ stag_status stag_polyakov_loop(stag_handle c, double* re, double* im) {
     const double ns = 3.0 * c->g.nx * c->g.ny * c->g.nz;
     if (re) *re = c->scal_host[0] / ns;
     if (im) *im = c->scal_host[1] / ns;
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_chiral_condensate(stag_handle c, double mass, double tol, int maxiter, int n_noise, uint64_t seed,
@@ -680,7 +687,7 @@ stag_status stag_chiral_condensate(stag_handle c, double mass, double tol, int m
         return fail(c, STAG_ERR_INVALID_ARG, "need mass > 0, tol > 0, maxiter >= 1, n_noise >= 1 and mean_out");
     const double residue = 1.0, pole = 0.0;
     const stag_rational r{1, 0.0, &residue, &pole};
-    if ((e = enter(c))) return e;
+    if ((e = begin_internal(c))) return e;
     const double V = 2.0 * c->g.vh;
     double sum = 0.0, sum2 = 0.0;
     for (int k = 0; k < n_noise; ++k) {
@@ -711,37 +718,41 @@ stag_status stag_kinetic_energy(stag_handle c, const void* mom, double* K) {
     stag_status e = check_common(c, false);
     if (e) return e;
     if (!aligned16(mom) || !K) return fail(c, STAG_ERR_INVALID_ARG, "mom NULL/misaligned or K_out NULL");
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     if ((e = kinetic_impl(c, (const double*)mom, K))) return e;
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_link_update(stag_handle c, const void* mom, double dt) {
     stag_status e = check_common(c, true);
     if (e) return e;
     if (!aligned16(mom) || !std::isfinite(dt)) return fail(c, STAG_ERR_INVALID_ARG, "mom NULL/misaligned or dt not finite");
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     launch_link_update(c->g, c->links, (const double*)mom, dt, c->s);
     links_changed(c);
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_random_momentum(stag_handle c, uint64_t seed, uint64_t traj, void* mom) {
     stag_status e = check_common(c, false);
     if (e) return e;
     if (!aligned16(mom)) return fail(c, STAG_ERR_INVALID_ARG, "mom NULL or misaligned");
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     launch_random_momentum(c->g, seed, traj, (double*)mom, c->s);
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_random_source(stag_handle c, uint64_t seed, uint64_t traj, void* xi) {
     stag_status e = check_common(c, false);
     if (e) return e;
     if (!aligned16(xi)) return fail(c, STAG_ERR_INVALID_ARG, "xi NULL or misaligned");
-    if ((e = enter(c))) return e;
+    CallerStream on(c);
+    if ((e = on.begin())) return e;
     launch_random_source(c->g, seed, traj, (double2*)xi, c->s);
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_philox(const uint32_t ctr[4], const uint32_t key[2], size_t n, uint32_t* out, void* stream) {
@@ -796,7 +807,7 @@ stag_status stag_md_trajectory(stag_handle c, const stag_hmc_params* p, stag_tra
     if (ferm && (p->spectrum_lo != 0.0 || p->spectrum_hi != 0.0) &&
         !(std::isfinite(p->spectrum_lo) && std::isfinite(p->spectrum_hi) && p->spectrum_lo < p->spectrum_hi))
         return fail(c, STAG_ERR_INVALID_ARG, "spectrum interval must be finite with lo < hi (or both 0)");
-    if ((e = enter(c))) return e;
+    if ((e = begin_internal(c))) return e;
     const Geom& g = c->g;
     const size_t mb = (size_t)64 * g.vh * sizeof(double);
     const size_t lb = (size_t)72 * g.vh * sizeof(double2);
