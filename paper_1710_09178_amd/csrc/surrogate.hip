@@ -13,6 +13,7 @@
 // the next layer, so the forward pass needs no data movement between layers.
 // Only the weight gradients (a sum over links, i.e. over the lane%16 index)
 // go through an LDS transpose.
+#include <algorithm>
 #include <cstring>
 #include <vector>
 
@@ -51,12 +52,8 @@ __device__ __forceinline__ void wave_sync() {
 }
 __device__ __forceinline__ f4 mfma(s4 a, s4 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ s4 pack4(float a, float b, float c, float d) {
-    s4 r;
-    r.x = (short)f2bf(a);
-    r.y = (short)f2bf(b);
-    r.z = (short)f2bf(c);
-    r.w = (short)f2bf(d);
-    return r;
+    typedef __bf16 b4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(s4, __builtin_convertvector(f4{a, b, c, d}, b4));  // v_cvt_pk_bf16_f32
 }
 
 // ---------------------------------------------------------------------------
@@ -153,23 +150,37 @@ __global__ __launch_bounds__(kBlock) void k_sur_features(Geom g, const double2* 
 }
 
 // ---------------------------------------------------------------------------
-// Weights staged in LDS as bf16, row-major [out][in].
+// Weights staged in LDS as bf16, row-major [out][in], and (for the backward
+// pass) transposed, so that every operand is an 8-byte read.  Rows of HD entries
+// are LD apart and the transposes of a tile LT: at 128 and 32 bytes the 16 rows of
+// an operand, or the rows a wave writes at once, would meet in the same banks.
+constexpr int LD = HD + 8, LT = 16 + 4;
 struct WLds {
     unsigned short w1[HD * FI];
-    unsigned short w2[HD * HD];
-    unsigned short w3[16 * HD];  // rows 8..15 zero
+    unsigned short w2[HD * LD];
+    unsigned short w3[16 * LD];  // rows 8..15 zero
     float b1[HD], b2[HD], b3[16];
+};
+struct WTLds {
+    unsigned short w2t[HD * LD];
+    unsigned short w3t[HD * 16];
 };
 
 __device__ void stage_weights(WLds& W, const float* __restrict__ prm) {
     for (int i = threadIdx.x; i < HD * FI; i += blockDim.x) W.w1[i] = f2bf(prm[OW1 + i]);
-    for (int i = threadIdx.x; i < HD * HD; i += blockDim.x) W.w2[i] = f2bf(prm[OW2 + i]);
-    for (int i = threadIdx.x; i < 16 * HD; i += blockDim.x) W.w3[i] = i < NO * HD ? f2bf(prm[OW3 + i]) : 0;
+    for (int i = threadIdx.x; i < HD * HD; i += blockDim.x) W.w2[i / HD * LD + i % HD] = f2bf(prm[OW2 + i]);
+    for (int i = threadIdx.x; i < 16 * HD; i += blockDim.x)
+        W.w3[i / HD * LD + i % HD] = i < NO * HD ? f2bf(prm[OW3 + i]) : 0;
     for (int i = threadIdx.x; i < HD; i += blockDim.x) {
         W.b1[i] = prm[OB1 + i];
         W.b2[i] = prm[OB2 + i];
     }
     for (int i = threadIdx.x; i < 16; i += blockDim.x) W.b3[i] = i < NO ? prm[OB3 + i] : 0.f;
+}
+// (after stage_weights and a barrier)
+__device__ void transpose_weights(WTLds& T, const WLds& W) {
+    for (int i = threadIdx.x; i < HD * HD; i += blockDim.x) T.w2t[i / HD * LD + i % HD] = W.w2[i % HD * LD + i / HD];
+    for (int i = threadIdx.x; i < HD * 16; i += blockDim.x) T.w3t[i] = W.w3[i % 16 * LD + i / 16];
 }
 
 // A operand of rows [r0, r0+16) and columns [k0, k0+16) of a row-major bf16
@@ -178,40 +189,42 @@ __device__ __forceinline__ s4 a_tile(const unsigned short* M, int ld, int r0, in
     const int l = threadIdx.x & 63;
     return *(const s4*)(M + (size_t)(r0 + (l & 15)) * ld + k0 + 4 * (l >> 4));
 }
-// A operand of the transposed matrix: lane l holds M[k0 + 4*(l/16)+v][r0 + l%16].
-__device__ __forceinline__ s4 at_tile(const unsigned short* M, int ld, int r0, int k0) {
-    const int l = threadIdx.x & 63;
-    const int r = r0 + (l & 15), k = k0 + 4 * (l >> 4);
-    s4 o;
-    o.x = (short)M[(size_t)(k + 0) * ld + r];
-    o.y = (short)M[(size_t)(k + 1) * ld + r];
-    o.z = (short)M[(size_t)(k + 2) * ld + r];
-    o.w = (short)M[(size_t)(k + 3) * ld + r];
-    return o;
-}
-
 // Per-wave scratch for the transposes of one 16-link tile.
 struct WaveLds {
-    unsigned short h1T[HD * 16], h2T[HD * 16], dz2T[HD * 16], dz1T[HD * 16], fT[FI * 16], dcT[16 * 16];
+    unsigned short h1T[HD * LT], h2T[HD * LT], dz2T[HD * LT], dz1T[HD * LT], fT[FI * LT], dcT[16 * LT];
     float c[16][NO];
     float dc[16][4][NO];
 };
 
-// Forward pass of one 16-link tile (rows n0..n0+15 of the dataset).  Returns
-// the per-lane forward state; c (16 x 8) is left in W.c.
+// What a lane reads of a tile's rows: its quarter of the features of link `col`
+// and components 2 grp, 2 grp + 1 of the link's fields (and target).
+struct TileIn {
+    s4 fb;
+    float2 B[NCH], t;
+    __device__ __forceinline__ void load(const unsigned short* __restrict__ f, const float* __restrict__ Bp,
+                                         const float* __restrict__ target, long long tile, long long rows) {
+        const int l = threadIdx.x & 63, col = l & 15, grp = l >> 4;
+        const long long n = tile * 16 + col;
+        fb = s4{0, 0, 0, 0};
+        if (n >= rows) return;
+        fb = *(const s4*)(f + (size_t)n * FI + 4 * grp);
+#pragma unroll
+        for (int j = 0; j < NCH; ++j) B[j] = *(const float2*)(Bp + ((size_t)n * NCH + j) * 8 + 2 * grp);
+        if (target) t = *(const float2*)(target + (size_t)n * 8 + 2 * grp);
+    }
+};
+
+// Forward pass of one 16-link tile with the features fb (TileIn).  Returns the
+// per-lane forward state; the coefficients are left in c [16][8].
 struct Fwd {
     f4 z1[4], z2[4];
     s4 h1b[4], h2b[4];
     s4 fb;
 };
 
-__device__ __forceinline__ void forward_tile(const WLds& W, WaveLds& S, const unsigned short* __restrict__ f, size_t n0,
-                                             int nvalid, Fwd& F) {
+__device__ __forceinline__ void forward_tile(const WLds& W, float (*c)[NO], s4 fb, Fwd& F) {
     const int l = threadIdx.x & 63, col = l & 15, grp = l >> 4;
-    if (col < nvalid)
-        F.fb = *(const s4*)(f + (n0 + col) * FI + 4 * grp);
-    else
-        F.fb = s4{0, 0, 0, 0};
+    F.fb = fb;
 #pragma unroll
     for (int hb = 0; hb < 4; ++hb) {
         f4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -228,7 +241,7 @@ __device__ __forceinline__ void forward_tile(const WLds& W, WaveLds& S, const un
     for (int ob = 0; ob < 4; ++ob) {
         f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) acc = mfma(a_tile(W.w2, HD, 16 * ob, 16 * kb), F.h1b[kb], acc);
+        for (int kb = 0; kb < 4; ++kb) acc = mfma(a_tile(W.w2, LD, 16 * ob, 16 * kb), F.h1b[kb], acc);
         float h[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -239,29 +252,39 @@ __device__ __forceinline__ void forward_tile(const WLds& W, WaveLds& S, const un
     }
     f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) acc = mfma(a_tile(W.w3, HD, 0, 16 * kb), F.h2b[kb], acc);
+    for (int kb = 0; kb < 4; ++kb) acc = mfma(a_tile(W.w3, LD, 0, 16 * kb), F.h2b[kb], acc);
     if (grp < 2)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) S.c[col][4 * grp + v] = acc[v] + W.b3[4 * grp + v];
+        for (int v = 0; v < 4; ++v) c[col][4 * grp + v] = acc[v] + W.b3[4 * grp + v];
 }
 
-// Loss, gradients and forces over a dataset slice.  One wave per 16-link tile
+// Loss and (GRAD) gradients over a dataset slice.  One wave per 16-link tile
 // (grid-stride); per-wave partial gradients go to gpart[wave][NPAR], partial
-// losses to lpart[wave].  force_out: optional F (rows x 8).
+// losses to lpart[wave].  The partition fixes the order of the sums, so there is
+// one wave per SIMD, bound by its own chain of some 1500 instructions per tile
+// (64 of them divisions): 61 us for the 8192 tiles of 16^3x8, and 80 us with the
+// rows read where they are used, operands of the backward pass gathered by
+// halves from rows 128 bytes apart, and accumulators copied round a branch.
+template <bool GRAD>
 __global__ __launch_bounds__(64 * kWavesSur) void k_sur_train(const unsigned short* __restrict__ f,
                                                               const float* __restrict__ B,
                                                               const float* __restrict__ target, long long rows,
                                                               double inv_rows, const float* __restrict__ prm,
-                                                              float* __restrict__ gpart, double* __restrict__ lpart,
-                                                              int want_grad) {
+                                                              float* __restrict__ gpart,
+                                                              double* __restrict__ lpart) {
     __shared__ WLds W;
+    __shared__ WTLds WT;
     __shared__ WaveLds SW[kWavesSur];
-    stage_weights(W, prm);
-    __syncthreads();
     const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, col = l & 15, grp = l >> 4;
     WaveLds& S = SW[wave];
     const long long gw = (long long)blockIdx.x * kWavesSur + wave;
     const long long nw = (long long)gridDim.x * kWavesSur;
+    TileIn next;  // the rows of a tile are read one tile ahead
+    next.load(f, B, target, gw, rows);
+    stage_weights(W, prm);
+    __syncthreads();
+    transpose_weights(WT, W);
+    __syncthreads();
     f4 G2[4][4], G1[4], G3[4];
     float db1[4][4], db2[4][4], db3[4];
 #pragma unroll
@@ -278,31 +301,30 @@ __global__ __launch_bounds__(64 * kWavesSur) void k_sur_train(const unsigned sho
     double loss = 0.0;
     const long long ntiles = (rows + 15) / 16;
     for (long long tile = gw; tile < ntiles; tile += nw) {
-        const size_t n0 = (size_t)tile * 16;
-        const int nvalid = (int)(rows - (long long)n0 < 16 ? rows - (long long)n0 : 16);
+        const int nvalid = (int)(rows - tile * 16 < 16 ? rows - tile * 16 : 16);
+        const TileIn in = next;
+        next.load(f, B, target, tile + nw, rows);
         Fwd F;
-        forward_tile(W, S, f, n0, nvalid, F);
+        forward_tile(W, S.c, in.fb, F);
         wave_sync();
         // force, loss and dL/dc: lane (col, grp) handles components a = 2 grp, 2 grp + 1
         float dcp[NO];
 #pragma unroll
         for (int j = 0; j < NO; ++j) dcp[j] = 0.f;
         if (col < nvalid) {
-            const size_t n = n0 + col;
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
-                const int a = 2 * grp + q;
                 float Fa = 0.f;
 #pragma unroll
-                for (int j = 0; j < NCH; ++j) Fa += S.c[col][j] * B[(n * NCH + j) * 8 + a];
-                const float d = Fa - target[n * 8 + a];
+                for (int j = 0; j < NCH; ++j) Fa += S.c[col][j] * (q ? in.B[j].y : in.B[j].x);
+                const float d = Fa - (q ? in.t.y : in.t.x);
                 loss += (double)d * (double)d;
                 const float dF = (float)(2.0 * inv_rows) * d;
 #pragma unroll
-                for (int j = 0; j < NCH; ++j) dcp[j] += dF * B[(n * NCH + j) * 8 + a];
+                for (int j = 0; j < NCH; ++j) dcp[j] += dF * (q ? in.B[j].y : in.B[j].x);
             }
         }
-        if (!want_grad) {
+        if constexpr (!GRAD) {
             wave_sync();
             continue;
         }
@@ -325,7 +347,7 @@ __global__ __launch_bounds__(64 * kWavesSur) void k_sur_train(const unsigned sho
 #pragma unroll
         for (int hb = 0; hb < 4; ++hb) {
             f4 acc = {0.f, 0.f, 0.f, 0.f};
-            acc = mfma(at_tile(W.w3, HD, 16 * hb, 0), dcb, acc);
+            acc = mfma(a_tile(WT.w3t, 16, 16 * hb, 0), dcb, acc);
 #pragma unroll
             for (int v = 0; v < 4; ++v) dz2[hb][v] = acc[v] * dsilu_f(F.z2[hb][v]);
             dz2b[hb] = pack4(dz2[hb][0], dz2[hb][1], dz2[hb][2], dz2[hb][3]);
@@ -338,7 +360,7 @@ __global__ __launch_bounds__(64 * kWavesSur) void k_sur_train(const unsigned sho
         for (int ib = 0; ib < 4; ++ib) {
             f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int kb = 0; kb < 4; ++kb) acc = mfma(at_tile(W.w2, HD, 16 * ib, 16 * kb), dz2b[kb], acc);
+            for (int kb = 0; kb < 4; ++kb) acc = mfma(a_tile(WT.w2t, LD, 16 * ib, 16 * kb), dz2b[kb], acc);
             float dz1[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -354,30 +376,30 @@ __global__ __launch_bounds__(64 * kWavesSur) void k_sur_train(const unsigned sho
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int h = 16 * hb + 4 * grp + v;
-                S.h1T[h * 16 + col] = (unsigned short)F.h1b[hb][v];
-                S.h2T[h * 16 + col] = (unsigned short)F.h2b[hb][v];
-                S.dz2T[h * 16 + col] = (unsigned short)dz2b[hb][v];
-                S.dz1T[h * 16 + col] = (unsigned short)dz1b[hb][v];
+                S.h1T[h * LT + col] = (unsigned short)F.h1b[hb][v];
+                S.h2T[h * LT + col] = (unsigned short)F.h2b[hb][v];
+                S.dz2T[h * LT + col] = (unsigned short)dz2b[hb][v];
+                S.dz1T[h * LT + col] = (unsigned short)dz1b[hb][v];
             }
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            S.fT[(4 * grp + v) * 16 + col] = (unsigned short)F.fb[v];
-            S.dcT[(4 * grp + v) * 16 + col] = (unsigned short)dcb[v];
+            S.fT[(4 * grp + v) * LT + col] = (unsigned short)F.fb[v];
+            S.dcT[(4 * grp + v) * LT + col] = (unsigned short)dcb[v];
         }
         wave_sync();
 #pragma unroll
         for (int ob = 0; ob < 4; ++ob) {
-            const s4 a2 = a_tile(S.dz2T, 16, 16 * ob, 0);
+            const s4 a2 = a_tile(S.dz2T, LT, 16 * ob, 0);
 #pragma unroll
-            for (int ib = 0; ib < 4; ++ib) G2[ob][ib] = mfma(a2, a_tile(S.h1T, 16, 16 * ib, 0), G2[ob][ib]);
-            G1[ob] = mfma(a_tile(S.dz1T, 16, 16 * ob, 0), a_tile(S.fT, 16, 0, 0), G1[ob]);
-            G3[ob] = mfma(a_tile(S.dcT, 16, 0, 0), a_tile(S.h2T, 16, 16 * ob, 0), G3[ob]);
+            for (int ib = 0; ib < 4; ++ib) G2[ob][ib] = mfma(a2, a_tile(S.h1T, LT, 16 * ib, 0), G2[ob][ib]);
+            G1[ob] = mfma(a_tile(S.dz1T, LT, 16 * ob, 0), a_tile(S.fT, LT, 0, 0), G1[ob]);
+            G3[ob] = mfma(a_tile(S.dcT, LT, 0, 0), a_tile(S.h2T, LT, 16 * ob, 0), G3[ob]);
         }
         wave_sync();
     }
     // per-wave partials (fixed order: wave index)
-    if (want_grad) {
+    if constexpr (GRAD) {
         float* out = gpart + (size_t)gw * NPAR;
         // G tiles: lane holds rows 4 grp + v of column col
 #pragma unroll
@@ -422,28 +444,32 @@ __global__ __launch_bounds__(64 * kWavesSur) void k_sur_train(const unsigned sho
 }
 
 // Forces F = sum_j c_j B_j of the current gauge field, written (dt == 0) or
-// added (dt != 0, times dt) to the internal momentum layout.
+// added (dt != 0, times dt) to the internal momentum layout.  16^3x8: 23 us, 42 MB
+// (48 us with 256 blocks, which scratch for gradients held to two per CU).
 __global__ __launch_bounds__(64 * kWavesSur) void k_sur_apply(Geom g, const unsigned short* __restrict__ f,
                                                               const float* __restrict__ B, const float* __restrict__ prm,
                                                               double* __restrict__ mom, double dt) {
     __shared__ WLds W;
-    __shared__ WaveLds SW[kWavesSur];
-    stage_weights(W, prm);
-    __syncthreads();
+    __shared__ float SC[kWavesSur][16][NO];
     const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, col = l & 15, grp = l >> 4;
-    WaveLds& S = SW[wave];
+    float(*c)[NO] = SC[wave];
     const long long rows = 8LL * g.vh;
     const long long ntiles = (rows + 15) / 16;
-    const long long gw = (long long)blockIdx.x * kWavesSur + wave;
+    // consecutive blocks of an XCD take consecutive tiles: they share the lines of mom
+    const long long gw = (long long)xcd_tile(blockIdx.x, gridDim.x) * kWavesSur + wave;
     const long long nw = (long long)gridDim.x * kWavesSur;
+    TileIn next;
+    next.load(f, B, nullptr, gw, rows);
+    stage_weights(W, prm);
+    __syncthreads();
     for (long long tile = gw; tile < ntiles; tile += nw) {
-        const size_t n0 = (size_t)tile * 16;
-        const int nvalid = (int)(rows - (long long)n0 < 16 ? rows - (long long)n0 : 16);
+        const TileIn in = next;
+        next.load(f, B, nullptr, tile + nw, rows);
         Fwd F;
-        forward_tile(W, S, f, n0, nvalid, F);
+        forward_tile(W, c, in.fb, F);
         wave_sync();
-        if (col < nvalid) {
-            const size_t n = n0 + col;
+        const size_t n = (size_t)tile * 16 + col;
+        if ((long long)n < rows) {
             const int lsite = (int)(n >> 2), mu = (int)(n & 3);
             const int x = lsite % g.nx, r1 = lsite / g.nx;
             const int y = r1 % g.ny, r2 = r1 / g.ny;
@@ -454,7 +480,7 @@ __global__ __launch_bounds__(64 * kWavesSur) void k_sur_apply(Geom g, const unsi
                 const int a = 2 * grp + q;
                 float Fa = 0.f;
 #pragma unroll
-                for (int j = 0; j < NCH; ++j) Fa += S.c[col][j] * B[(n * NCH + j) * 8 + a];
+                for (int j = 0; j < NCH; ++j) Fa += c[col][j] * (q ? in.B[j].y : in.B[j].x);
                 double* m = mom + mom_off(g, par, mu, a) + cb;
                 if (dt == 0.0)
                     *m = (double)Fa;
@@ -492,31 +518,14 @@ __global__ void k_sur_gsum(const float* __restrict__ gpart, int nwaves, float* _
     const int per = (nwaves + kGradChunks - 1) / kGradChunks;
     const int w0 = blockIdx.y * per, w1 = min(nwaves, w0 + per);
     float g = 0.f;
+#pragma unroll 8
     for (int w = w0; w < w1; ++w) g += gpart[(size_t)w * NPAR + k];
     gpart2[(size_t)blockIdx.y * NPAR + k] = g;
 }
 
-// Second stage (chunks in order) and one Adam step.
-__global__ void k_sur_adam(const float* __restrict__ gpart2, float* __restrict__ prm, float* __restrict__ m,
-                           float* __restrict__ v, float* __restrict__ grad_out, float lr, float b1, float b2, float eps,
-                           float c1, float c2, int step) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= NPAR) return;
-    float gsum = 0.f;
-    for (int c = 0; c < kGradChunks; ++c) gsum += gpart2[(size_t)c * NPAR + k];
-    if (grad_out) grad_out[k] = gsum;
-    if (!step) return;
-    const float mk = b1 * m[k] + (1.f - b1) * gsum;
-    const float vk = b2 * v[k] + (1.f - b2) * gsum * gsum;
-    m[k] = mk;
-    v[k] = vk;
-    prm[k] -= lr * (mk / c1) / (sqrtf(vk / c2) + eps);
-}
-
-// out[0] = sum of the n partials (one block, fixed order); out[1] += the same
-// sum (epoch accumulator), or out[1] = 0 first when reset is set
-__global__ __launch_bounds__(kBlock) void k_sum_double(const double* __restrict__ p, int n, double* __restrict__ out,
-                                                       int reset) {
+// The loss: out[0] = sum of the n partials (one block, fixed order); out[1] += the
+// same sum (epoch accumulator), or out[1] = 0 first when reset is set.
+__device__ __forceinline__ void sum_loss(const double* __restrict__ p, int n, double* __restrict__ out, int reset) {
     double v[1] = {0.0};
     for (int i = threadIdx.x; i < n; i += kBlock) v[0] += p[i];
     __shared__ double lds[4];
@@ -525,6 +534,35 @@ __global__ __launch_bounds__(kBlock) void k_sum_double(const double* __restrict_
         out[0] = v[0];
         out[1] = (reset ? 0.0 : out[1]) + v[0];
     }
+}
+__global__ __launch_bounds__(kBlock) void k_sum_loss(const double* __restrict__ p, int n, double* __restrict__ out,
+                                                     int reset) {
+    sum_loss(p, n, out, reset);
+}
+
+// Second stage (chunks in order) and one Adam step; the last block sums the loss.
+__global__ __launch_bounds__(kBlock) void k_sur_adam(const float* __restrict__ gpart2, float* __restrict__ prm,
+                                                     float* __restrict__ m, float* __restrict__ v,
+                                                     float* __restrict__ grad_out, float lr, float b1, float b2,
+                                                     float eps, float c1, float c2, int step,
+                                                     const double* __restrict__ lpart, int nl,
+                                                     double* __restrict__ lsum, int reset) {
+    if (blockIdx.x == gridDim.x - 1) {
+        sum_loss(lpart, nl, lsum, reset);
+        return;
+    }
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= NPAR) return;
+    float gsum = 0.f;
+#pragma unroll
+    for (int c = 0; c < kGradChunks; ++c) gsum += gpart2[(size_t)c * NPAR + k];
+    if (grad_out) grad_out[k] = gsum;
+    if (!step) return;
+    const float mk = b1 * m[k] + (1.f - b1) * gsum;
+    const float vk = b2 * v[k] + (1.f - b2) * gsum * gsum;
+    m[k] = mk;
+    v[k] = vk;
+    prm[k] -= lr * (mk / c1) / (sqrtf(vk / c2) + eps);
 }
 
 }  // namespace
@@ -590,18 +628,21 @@ void features_into(stag_surrogate* s, int k) {
 // loss (and gradient sum / Adam step) over `rows` dataset rows starting at slot k
 void train_pass(stag_surrogate* s, int k, long long rows, bool grad, int adam_step, float lr, bool reset = true) {
     stag_ctx* c = s->lat;
-    k_sur_train<<<s->nblocks, 64 * kWavesSur, 0, c->s>>>(slot_f(s, k), slot_B(s, k), slot_t(s, k), rows,
-                                                         1.0 / (double)rows, s->prm, s->gpart, s->lpart, grad ? 1 : 0);
+    auto* train = grad ? k_sur_train<true> : k_sur_train<false>;
+    train<<<s->nblocks, 64 * kWavesSur, 0, c->s>>>(slot_f(s, k), slot_B(s, k), slot_t(s, k), rows,
+                                                   1.0 / (double)rows, s->prm, s->gpart, s->lpart);
     if (grad) {
         const float b1 = 0.9f, b2 = 0.999f;
         const float c1 = adam_step ? 1.f - powf(b1, (float)adam_step) : 1.f;
         const float c2 = adam_step ? 1.f - powf(b2, (float)adam_step) : 1.f;
         k_sur_gsum<<<dim3((NPAR + 255) / 256, kGradChunks), 256, 0, c->s>>>(s->gpart, s->nblocks * kWavesSur,
                                                                              s->gpart2);
-        k_sur_adam<<<(NPAR + 255) / 256, 256, 0, c->s>>>(s->gpart2, s->prm, s->m, s->v, s->grad, lr, b1, b2, 1e-8f, c1,
-                                                         c2, adam_step);
+        k_sur_adam<<<(NPAR + kBlock - 1) / kBlock + 1, kBlock, 0, c->s>>>(
+            s->gpart2, s->prm, s->m, s->v, s->grad, lr, b1, b2, 1e-8f, c1, c2, adam_step, s->lpart,
+            s->nblocks * kWavesSur, s->lsum, reset ? 1 : 0);
+    } else {
+        k_sum_loss<<<1, kBlock, 0, c->s>>>(s->lpart, s->nblocks * kWavesSur, s->lsum, reset ? 1 : 0);
     }
-    k_sum_double<<<1, kBlock, 0, c->s>>>(s->lpart, s->nblocks * kWavesSur, s->lsum, reset ? 1 : 0);
 }
 
 }  // namespace
@@ -747,7 +788,10 @@ stag_status stag_surrogate_force(stag_surrogate_handle s, void* mom, double dt) 
     const int k = s->capacity;
     if (begin_model(c)) return sfail(s, STAG_ERR_HIP, c->err);
     features_into(s, k);
-    k_sur_apply<<<s->nblocks, 64 * kWavesSur, 0, c->s>>>(c->g, slot_f(s, k), slot_B(s, k), s->prm, (double*)mom, dt);
+    // four blocks fit a CU; with fewer tiles a wave each
+    const long long ntiles = (s->links + 15) / 16;
+    const int grid = (int)std::min<long long>(1024, (ntiles + kWavesSur - 1) / kWavesSur);
+    k_sur_apply<<<grid, 64 * kWavesSur, 0, c->s>>>(c->g, slot_f(s, k), slot_B(s, k), s->prm, (double*)mom, dt);
     SHIP(s, hipGetLastError());
     return STAG_OK;
 }
