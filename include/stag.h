@@ -550,9 +550,10 @@ stag_status stag_profile_samples(stag_handle h, int kind, float* us_out, int cap
 stag_status stag_set_fused_iteration(stag_handle h, int mode);
 /* How every FP64 operator application of h loads the links (and long links):
  * mode 1 (default) with non-temporal loads when the FP64 field(s) exceed
- * 512 MB -- they cannot stay in the 256 MB Infinity Cache between Dslash
- * launches, and streaming them past it keeps the shared vectors cached --
- * and plain loads otherwise; 0 always plain, 2 always non-temporal.  Results
+ * the 256 MB of the Infinity Cache -- streaming them past it keeps the shared
+ * vectors cached -- except for those of a launch's first and last tiles, which
+ * the next launch reads first, and plain loads otherwise; 0 always plain, 2
+ * always non-temporal.  Results
  * are bitwise the same in every mode.  STAG_ERR_INVALID_ARG for other modes. */
 stag_status stag_set_link_streaming(stag_handle h, int mode);
 /* Solvers replay each chunk of iterations from a hipGraph captured on first

@@ -169,7 +169,8 @@ __global__ __launch_bounds__(kBlock, TPS == 4 ? 3 : 2) void k_bdslash(BatchDev b
     constexpr int SB = kBlock / TPS;
     constexpr int DPT = 4 / TPS;
     using Rl = typename BPrec<V>::R;
-    const BTile tl = bd.tiles[blockIdx.x];
+    const int ti = out_par ? (int)blockIdx.x : turned(blockIdx.x, gridDim.x);
+    const BTile tl = bd.tiles[ti];
     if (inst_done && inst_done[tl.inst]) return;
     const BInst I = bd.inst[tl.inst];
     const Geom& g = I.g;
@@ -291,7 +292,7 @@ __global__ __launch_bounds__(kBlock, TPS == 4 ? 3 : 2) void k_bdslash(BatchDev b
             if (lane == 0)
 #pragma unroll
                 for (int k = 0; k < Epi::K; ++k)
-                    epi.part[((size_t)blockIdx.x * kMaxRhs + slice) * Epi::K + k] = v[k];
+                    epi.part[((size_t)ti * kMaxRhs + slice) * Epi::K + k] = v[k];
         }
     } else {
 #pragma unroll
@@ -310,7 +311,7 @@ __global__ __launch_bounds__(kBlock, TPS == 4 ? 3 : 2) void k_bdslash(BatchDev b
             for (int s = 1; s < TPS; ++s) v = cadd(v, part[((s * kMaxRhs + rh) * 3 + c) * SB + jj]);
             sums.item(epi, I, tl.inst, rh, bvec_off(I, R, rh, c) + site, v);
         }
-        sums.finish(epi, blockIdx.x);
+        sums.finish(epi, ti);
     }
 }
 
@@ -326,7 +327,8 @@ __global__ __launch_bounds__(kBlock) void k_bdslash8(BatchDev bd, const V* __res
                                                      const V* __restrict__ in, int out_par, Epi epi,
                                                      const int* __restrict__ inst_done) {
     using Rl = typename BPrec<V>::R;
-    const BTile tl = bd.tiles[blockIdx.x];
+    const int ti = out_par ? (int)blockIdx.x : turned(blockIdx.x, gridDim.x);
+    const BTile tl = bd.tiles[ti];
     if (inst_done && inst_done[tl.inst]) return;
     const BInst I = bd.inst[tl.inst];
     const Geom& g = I.g;
@@ -394,7 +396,7 @@ __global__ __launch_bounds__(kBlock) void k_bdslash8(BatchDev bd, const V* __res
             for (int c = 0; c < 3; ++c)
                 if ((3 * r + c) % 8 == h) sums.item(epi, I, tl.inst, r, bvec_off(I, R, r, c) + cb, a[c]);
     }
-    sums.finish(epi, blockIdx.x);
+    sums.finish(epi, ti);
 }
 
 template <class V, class Epi>

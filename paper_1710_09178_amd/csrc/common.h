@@ -218,6 +218,15 @@ __host__ __device__ __forceinline__ int xcd_tile_slab(int b, int nb, const Geom&
     return xcd_tile(b, nb);
 }
 
+// Block b of nb in the opposite order, on the same XCD.  The two applications of
+// an operator read the same links: the second begins where the first ended, with
+// what the first left in the caches, and the next one's first where it ended
+// (A psi at 32^3x16, 302 MB of links: 117 -> 101 us; solve at 32^3x8: 2.4%).
+__device__ __forceinline__ int turned(int b, int nb) {
+    const int m = nb & ~7;  // whole rounds of the eight XCDs
+    return b < m ? m - 8 - (b & ~7) + (b & 7) : b;
+}
+
 // ---------------------------------------------------------------------------
 // Multi-shift CG state kept on the device (scalars never leave the GPU inside
 // the iteration loop).

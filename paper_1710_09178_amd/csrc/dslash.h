@@ -19,6 +19,7 @@ struct LinkSet {
     const void* h12;         // __half2 [2][4][6][Vh]
     int naik;
     int nt;                  // FP64 links loaded non-temporally (fields larger than the Infinity Cache)
+    int turn;                // ... except those of this many output sites at either end of a launch
     double c1, c3;
     const double2* ld18;
     const double2* ld12;

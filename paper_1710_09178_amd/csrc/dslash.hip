@@ -189,6 +189,33 @@ struct EpiResid {
     }
 };
 
+// The same operator with plain loads (streams: whether that differs).
+template <class Link>
+struct PlainLoads {
+    static constexpr bool streams = false;
+};
+template <>
+struct PlainLoads<LinkD18T<true>> {
+    static constexpr bool streams = true;
+    static __device__ __forceinline__ int turn(const LinkD18T<true>& l) { return l.turn; }
+    static __device__ __forceinline__ LinkD18 of(const LinkD18T<true>& l) { return LinkD18{l.u}; }
+};
+template <>
+struct PlainLoads<LinkD12T<true>> {
+    static constexpr bool streams = true;
+    static __device__ __forceinline__ int turn(const LinkD12T<true>& l) { return l.turn; }
+    static __device__ __forceinline__ LinkD12 of(const LinkD12T<true>& l) { return LinkD12{l.u}; }
+};
+template <class Link>
+struct PlainLoads<NaikOp<Link>> {
+    static constexpr bool streams = PlainLoads<Link>::streams;
+    static __device__ __forceinline__ int turn(const NaikOp<Link>& l) { return PlainLoads<Link>::turn(l.one); }
+    static __device__ __forceinline__ auto of(const NaikOp<Link>& l) {
+        auto one = PlainLoads<Link>::of(l.one);
+        return NaikOp<decltype(one)>{one, PlainLoads<Link>::of(l.three), l.c1, l.c3};
+    }
+};
+
 template <int TPS, class Link, class Epi>
 __global__ __launch_bounds__(kBlock) void k_dslash(Geom g, Link L, const typename Link::C* __restrict__ in,
                                                    int out_par, Epi epi, const int* __restrict__ gate) {
@@ -200,7 +227,7 @@ __global__ __launch_bounds__(kBlock) void k_dslash(Geom g, Link L, const typenam
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int slice = wave % TPS, sgrp = wave / TPS;
     const int j = sgrp * 64 + lane;
-    const int tile = xcd_tile_slab(blockIdx.x, gridDim.x, g, SB);
+    const int tile = xcd_tile_slab(out_par ? (int)blockIdx.x : turned(blockIdx.x, gridDim.x), gridDim.x, g, SB);
     const int cb = tile * SB + j;
     C acc[3];
 #pragma unroll
@@ -208,8 +235,19 @@ __global__ __launch_bounds__(kBlock) void k_dslash(Geom g, Link L, const typenam
     if (cb < g.vh) {
         int x, y, z, t;
         cb_coords(g, out_par, cb, x, y, z, t);
+        auto hops = [&](const auto& links) {
 #pragma unroll
-        for (int d = 0; d < DPT; ++d) hop(g, L, in, out_par, slice * DPT + d, cb, x, y, z, t, acc);
+            for (int d = 0; d < DPT; ++d) hop(g, links, in, out_par, slice * DPT + d, cb, x, y, z, t, acc);
+        };
+        if constexpr (PlainLoads<Link>::streams) {
+            const int end = min((int)blockIdx.x, (int)(gridDim.x - 1 - blockIdx.x));
+            if (end * SB < PlainLoads<Link>::turn(L))
+                hops(PlainLoads<Link>::of(L));
+            else
+                hops(L);
+        } else {
+            hops(L);
+        }
     }
 #pragma unroll
     for (int c = 0; c < 3; ++c) part[(slice * 3 + c) * SB + j] = acc[c];
@@ -532,13 +570,13 @@ void with_link64_nt(const LinkSet& ls, Fn fn) {
     using D12 = LinkD12T<NT>;
     if (ls.naik) {
         if (ls.fmt64 == STAG_LINKS_F64_12)
-            fn(NaikOp<D12>{D12{ls.d12}, D12{ls.ld12}, ls.c1, ls.c3});
+            fn(NaikOp<D12>{D12{ls.d12, ls.turn}, D12{ls.ld12}, ls.c1, ls.c3});
         else
-            fn(NaikOp<D18>{D18{ls.d18}, D18{ls.ld18}, ls.c1, ls.c3});
+            fn(NaikOp<D18>{D18{ls.d18, ls.turn}, D18{ls.ld18}, ls.c1, ls.c3});
     } else if (ls.fmt64 == STAG_LINKS_F64_12) {
-        fn(D12{ls.d12});
+        fn(D12{ls.d12, ls.turn});
     } else {
-        fn(D18{ls.d18});
+        fn(D18{ls.d18, ls.turn});
     }
 }
 template <class Fn>

@@ -14,15 +14,25 @@ namespace stag {
 
 namespace {
 
+// conj(a b - c d); in FP64 with the multiply-adds spelt out, so that every kernel
+// that rebuilds a row, and each of a kernel's kinds of load, rounds alike
+__device__ __forceinline__ double2 minor_conj(double2 a, double2 b, double2 c, double2 d) {
+    const double x = fma(c.y, d.y, fma(-c.x, d.x, fma(-a.y, b.y, a.x * b.x)));
+    const double y = fma(-c.y, d.x, fma(-c.x, d.y, fma(a.y, b.x, a.x * b.y)));
+    return make_double2(x, -y);
+}
+__device__ __forceinline__ float2 minor_conj(float2 a, float2 b, float2 c, float2 d) {
+    return cconj(csub(cmul(a, b), cmul(c, d)));
+}
 template <class C>
 __device__ __forceinline__ void rebuild_row2(C (&m)[9]) {
-    m[6] = cconj(csub(cmul(m[1], m[5]), cmul(m[2], m[4])));
-    m[7] = cconj(csub(cmul(m[2], m[3]), cmul(m[0], m[5])));
-    m[8] = cconj(csub(cmul(m[0], m[4]), cmul(m[1], m[3])));
+    m[6] = minor_conj(m[1], m[5], m[2], m[4]);
+    m[7] = minor_conj(m[2], m[3], m[0], m[5]);
+    m[8] = minor_conj(m[0], m[4], m[1], m[3]);
 }
 
 // FP64 link entry; NT: a non-temporal load, for link fields larger than the
-// Infinity Cache, which every Dslash streams once from HBM: they then do not
+// Infinity Cache, most of which every Dslash streams from HBM: they then do not
 // evict the vectors the neighbours share.
 template <bool NT>
 __device__ __forceinline__ double2 link_entry(const double2* p) {
@@ -40,6 +50,7 @@ struct LinkD18T {
     using C = double2;
     using R = double;
     const double2* __restrict__ u;
+    int turn = 0;  // NT: output sites at either end of a launch whose links are loaded plainly
     __device__ __forceinline__ void load(const Geom& g, int par, int mu, int cb, C (&m)[9]) const {
         const double2* p = u + link_off(g, par, mu, 0) + cb;
 #pragma unroll
@@ -53,6 +64,7 @@ struct LinkD12T {
     using C = double2;
     using R = double;
     const double2* __restrict__ u;
+    int turn = 0;  // NT: output sites at either end of a launch whose links are loaded plainly
     __device__ __forceinline__ void load(const Geom& g, int par, int mu, int cb, C (&m)[9]) const {
         const double2* p = u + link12_off(g, par, mu, 0) + cb;
 #pragma unroll

@@ -30,13 +30,18 @@ stag_status ensure_pool(stag_ctx* c, int n) {
     return STAG_OK;
 }
 
-// Link fields up to this size are served largely by the 256 MB Infinity
-// Cache between the Dslash launches of a solve: the 151 MB FP64 field of
-// 32^3x8 stays there, and even the 302 MB of links and long links of the
-// improved operator at 32^3x8 run 6% slower with non-temporal loads.  Larger
-// fields are streamed from HBM every time (48^3x16, 1.02 GB: D_oe 221 -> 201 us
-// with non-temporal loads).
-constexpr size_t kLinkCacheBytes = (size_t)512 << 20;
+// Link fields up to this size stay in the 256 MB Infinity Cache between the
+// Dslash launches of a solve (the 151 MB FP64 field of 32^3x8).  Larger ones are
+// streamed with non-temporal loads, except for about kTurnBytes at either end of
+// a launch: D_eo takes the tiles in the opposite order (turned), so it begins with
+// what D_oe ended with, and the next D_oe with what D_eo ended with.  A psi with
+// plain, non-temporal and these loads: 302 MB 100, 114 and 97 us; 453 MB 165, 167
+// and 152; 764 MB (48^3x12) 306, 293 and 280; 1.5 GB 631, 583 and 582.  12-pole
+// solves against a limit of 512 MB: 302 MB 16.6 against 17.5 ms, 453 MB 33.7
+// against 35.7 ms.  Turning 48 or 96 MB costs up to 2% of that at one end or the
+// other of these sizes, 160 MB 5%.
+constexpr size_t kLinkCacheBytes = (size_t)256 << 20;
+constexpr size_t kTurnBytes = (size_t)80 << 20;
 
 stag_status get_links(stag_ctx* c, int fmt32, LinkSet& ls) {
     const Geom& g = c->g;
@@ -52,6 +57,7 @@ stag_status get_links(stag_ctx* c, int fmt32, LinkSet& ls) {
         const size_t per_field = (size_t)2 * 4 * (c->fmt64 == STAG_LINKS_F64_12 ? 96 : 144) * g.vh;
         const size_t bytes = per_field * (c->naik ? 2 : 1);
         ls.nt = c->link_nt == 2 || (c->link_nt == 1 && bytes > kLinkCacheBytes);
+        if (c->link_nt == 1 && ls.nt) ls.turn = (int)(kTurnBytes / (bytes / g.vh));
     }
     stag_status e;
     if (c->fmt64 == STAG_LINKS_F64_12) {
