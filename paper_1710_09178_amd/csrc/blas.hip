@@ -110,7 +110,21 @@ __global__ __launch_bounds__(kBlock) void k_ms_step(int n3, V* __restrict__ ring
     // addresses below do not wait for the state
     const int n = sc.n, base = sc.base, L = sc.lag, slot = sc.slot;
     const MsIter& s = st->it[par];
-    const int iter = s.iter;
+    const int k = threadIdx.x;
+    // the state that wave 0 needs below, shift k in lane k, in the round trip of the
+    // loads that follow (read where it is needed it cost one of its own: 24^3x6 in
+    // FP32, whose step takes 8 us, 7.7 -> 7.5 ms per mixed solve)
+    const int iter = s.iter, bb_given = st->bb_given, maxiter = st->maxiter;
+    const double s_bb = s.bb, a_old = s.alpha_old, b_old = s.beta_old, tol2 = st->tol2;
+    double z = 0.0, zo = 0.0, shift = 0.0;
+    int was = 0, ipp = 0;
+    if (k < n) {
+        z = s.zeta[k];
+        zo = s.zeta_old[k];
+        shift = st->shift[k];
+        was = s.active[k];
+        ipp = s.iters_per_pole[k];
+    }
     // Partial sums of the previous launches (<r,r> of the step or init, and
     // the three dots of the operator): each thread issues its first loads all
     // together, then the loads of the base system's streams, which do not
@@ -166,10 +180,9 @@ __global__ __launch_bounds__(kBlock) void k_ms_step(int n3, V* __restrict__ ring
     // Wave 0 evaluates the iteration's scalars, one lane per shift (n <= 48 < 64):
     // every lane computes alpha and beta from the same broadcast totals, and the
     // freezing test, the stop decision and the shift list use wave ballots.
-    const int k = threadIdx.x;
     if (k < 64) {
         const double rr = __shfl(v[0], 0), pAp = __shfl(v[1], 0), rAp = __shfl(v[2], 0), ApAp = __shfl(v[3], 0);
-        const double bb = (iter == 0 && !st->bb_given) ? rr : s.bb;
+        const double bb = (iter == 0 && !bb_given) ? rr : s_bb;
         int nonfinite = !isfinite(rr);
         double alpha = 0.0, beta = 0.0;
         if (!nonfinite) {
@@ -182,17 +195,15 @@ __global__ __launch_bounds__(kBlock) void k_ms_step(int n3, V* __restrict__ ring
         int act = 0;
         double zn = 0.0, as = 0.0, bs = 0.0;
         if (k < n) {
-            act = s.active[k];
-            if (act && s.zeta[k] * s.zeta[k] * rr <= st->tol2 * bb) act = 0;
-            const double z = s.zeta[k], zo = s.zeta_old[k];
+            act = was;
+            if (act && z * z * rr <= tol2 * bb) act = 0;
             zn = z;
             if (k == base) {
                 zn = 1.0;
                 as = alpha;
                 bs = beta;
             } else if (act) {
-                const double a_old = s.alpha_old, b_old = s.beta_old;
-                zn = z * zo * a_old / (alpha * b_old * (zo - z) + zo * a_old * (1.0 + st->shift[k] * alpha));
+                zn = z * zo * a_old / (alpha * b_old * (zo - z) + zo * a_old * (1.0 + shift * alpha));
                 const double q = zn / z;
                 as = alpha * q;
                 bs = beta * q * q;
@@ -200,7 +211,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_step(int n3, V* __restrict__ ring
         }
         const unsigned long long any = __ballot(act != 0);
         if (any && !(isfinite(alpha) && isfinite(beta))) nonfinite = 1;
-        const int stop = nonfinite || !any || iter >= st->maxiter;
+        const int stop = nonfinite || !any || iter >= maxiter;
         // pending shifted updates: iterations iter - slot .. iter (.. iter - 1 when stopping)
         const int npend = stop ? slot : slot + 1;
         const int flush = npend > 0 && (stop || slot == L - 1);
@@ -223,9 +234,9 @@ __global__ __launch_bounds__(kBlock) void k_ms_step(int n3, V* __restrict__ ring
                 // the state of the next iteration (or the final one)
                 MsIter& o = stop ? st->fin : st->it[par ^ 1];
                 o.active[k] = act;
-                o.iters_per_pole[k] = (act && !stop) ? iter + 1 : (s.active[k] ? iter : s.iters_per_pole[k]);
-                o.zeta[k] = stop ? s.zeta[k] : zn;
-                o.zeta_old[k] = stop ? s.zeta_old[k] : s.zeta[k];
+                o.iters_per_pole[k] = (act && !stop) ? iter + 1 : (was ? iter : ipp);
+                o.zeta[k] = stop ? z : zn;
+                o.zeta_old[k] = stop ? zo : z;
                 if (!stop && !flush) {
                     st->hist[slot].as[k] = as;
                     st->hist[slot].bs[k] = bs;
@@ -248,8 +259,8 @@ __global__ __launch_bounds__(kBlock) void k_ms_step(int n3, V* __restrict__ ring
             sh_base_on = base_act;
             if (blockIdx.x == 0 && blockIdx.y == 0) {
                 MsIter& o = stop ? st->fin : st->it[par ^ 1];
-                o.alpha_old = stop ? s.alpha_old : alpha;
-                o.beta_old = stop ? s.beta_old : beta;
+                o.alpha_old = stop ? a_old : alpha;
+                o.beta_old = stop ? b_old : beta;
                 o.bb = bb;
                 o.rr = rr;
                 o.iter = stop ? iter : iter + 1;
