@@ -144,7 +144,8 @@ def cpu_baseline(U, b, rat, vh, lag, target_s=20.0):
 
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "dslash_oe_fp64_32c3x8_hbm_traffic.md")
 DSLASH_SOURCES = ["paper_1710_09178_amd/csrc/dslash.hip", "paper_1710_09178_amd/csrc/dslash.h",
-                  "paper_1710_09178_amd/csrc/common.h", "paper_1710_09178_amd/csrc/msfused.h"]
+                  "paper_1710_09178_amd/csrc/common.h", "paper_1710_09178_amd/csrc/msfused.h",
+                  "paper_1710_09178_amd/csrc/hop.h"]
 
 
 def measured_traffic(fused=True):
