@@ -253,12 +253,11 @@ struct ResStep {  // scalars of one shift in one step; a frozen shift has {0, 1,
 // 20^3x8 5.3 against 8.1 ms, 16^3x12 6.7 against 10.2 ms, 16^3x8 4.1 against
 // 8.0 ms.  A third block per CU (80 registers, 90 spilled) takes 18.8 us per
 // iteration where the loop takes 22 (24^3x6), and 15% more than two on the
-// lattices that two hold: not used.
-template <class Link>
-constexpr int kResWaves = sizeof(typename Link::C) == sizeof(float2) ? 4 : 2;  // per SIMD
-template <class Link, bool SHIFTS>
-__global__ __launch_bounds__(kResThreads, kResWaves<Link>) void k_resident(Geom g, Link L,
-                                                                           ResidentArgs<typename Link::C> a) {
+// lattices that two hold: not used.  Where one block per CU holds the grid, so
+// that its window's code keeps its registers, FP32 trajectories at 16^3x8 take
+// 27.9 ms instead of 34.1 (20 steps; FP64 32.5).  WAVES: per SIMD.
+template <class Link, bool SHIFTS, int WAVES>
+__global__ __launch_bounds__(kResThreads, WAVES) void k_resident(Geom g, Link L, ResidentArgs<typename Link::C> a) {
     using C = typename Link::C;
     using R = typename Link::R;
     using X = XElem<C>;
@@ -690,7 +689,7 @@ __global__ void k_fill_empty(u4v* __restrict__ p, size_t n) {
 // device; 0 where that is unknown).
 constexpr size_t kResHistMax = (size_t)2 * kLagMax * kMaxPoles * sizeof(ResStep);
 constexpr int kResDevices = 64;
-template <class Link, bool SHIFTS>
+template <class Link, bool SHIFTS, int WAVES>
 int capacity() {
     static std::atomic<int> known[kResDevices];  // capacity + 1
     int dev = -1, blocks = 0, cus = 0, coop = 0;
@@ -699,7 +698,7 @@ int capacity() {
     if (k) return k - 1;
     if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, (const void*)k_resident<Link, SHIFTS>,
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, (const void*)k_resident<Link, SHIFTS, WAVES>,
                                                      kResThreads, SHIFTS ? kResHistMax : 0) != hipSuccess) {
         (void)hipGetLastError();
         blocks = 0;
@@ -730,11 +729,23 @@ template <class V>
 bool single(const ResidentArgs<V>& a) {
     return sizeof(V) == sizeof(float2) && a.n == 1 && !a.b;
 }
+// The kernel for nb blocks, NULL where they do not fit: two waves per SIMD, or
+// four (a second block per CU) for FP32 where two do not hold the grid.  The
+// single system has the registers for four anyway.
+template <class Link, bool SHIFTS>
+const void* kernel_for(int nb) {
+    constexpr bool fp32 = sizeof(typename Link::C) == sizeof(float2);
+    if (nb > kResMax) return nullptr;
+    if constexpr (SHIFTS || !fp32)
+        if (nb <= capacity<Link, SHIFTS, 2>()) return (const void*)k_resident<Link, SHIFTS, 2>;
+    if constexpr (fp32)
+        if (nb <= capacity<Link, SHIFTS, 4>()) return (const void*)k_resident<Link, SHIFTS, 4>;
+    return nullptr;
+}
 template <bool SHIFTS, class V>
 bool fits(const Geom& g, const LinkSet& ls) {
     bool ok = false;
-    const int nb = resident_blocks(g);
-    with_link(ls, V{}, [&](auto L) { ok = nb <= kResMax && nb <= capacity<decltype(L), SHIFTS>(); });
+    with_link(ls, V{}, [&](auto L) { ok = kernel_for<decltype(L), SHIFTS>(resident_blocks(g)) != nullptr; });
     return ok;
 }
 
@@ -755,13 +766,14 @@ hipError_t launch_resident(const Geom& g, const LinkSet& ls, const ResidentArgs<
         Geom gg = g;
         ResidentArgs<V> aa = a;
         void* args[] = {&gg, &L, &aa};
-        const void* kernel = (const void*)k_resident<decltype(L), true>;
+        const void* kernel = kernel_for<decltype(L), true>(resident_blocks(g));
         size_t dyn = (size_t)2 * a.lag * a.n * sizeof(ResStep);
         if constexpr (sizeof(V) == sizeof(float2))
             if (single(a)) {
-                kernel = (const void*)k_resident<decltype(L), false>;
+                kernel = kernel_for<decltype(L), false>(resident_blocks(g));
                 dyn = 0;
             }
+        if (!kernel) return;
         err = hipLaunchCooperativeKernel(kernel, dim3(resident_blocks(g)), dim3(kResThreads), args, dyn, s);
     });
     return err;
