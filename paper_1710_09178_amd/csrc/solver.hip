@@ -853,6 +853,12 @@ stag_status ms_solve_mixed(stag_ctx* c, double mass, const stag_rational* r, dou
             res.iters += it;
             if (!conv) res.converged = 0;
         }
+        // the state is that of the last pole's refinement: r's coefficients
+        // again, for the caller's sum over the poles
+        int base;
+        HIP_OR_FAIL(c, hipStreamSynchronize(c->s));
+        init_state(c->st_host, r->n, r->pole, r->residue, r->c0, mass, tol, maxiter, base);
+        HIP_OR_FAIL(c, hipMemcpyAsync(c->st, c->st_host, sizeof(MsState), hipMemcpyHostToDevice, c->s));
     }
     for (int k = 0; k < r->n && ipp_out; ++k) ipp_out[k] = ipp[k];
     if (want_resid) {
