@@ -1,7 +1,8 @@
 // extern "C" entry points of libstag: handle management, argument checks,
 // field conversions, the multi-shift CG driver (Sec. 4), forces and the RHMC
-// trajectory (Sec. 3.1).  All device work goes to one internal stream that is
-// ordered after / before the caller's stream with events.
+// trajectory (Sec. 3.1).  Calls that loop or poll work on the handle's own
+// stream, ordered after / before the caller's with events; the others on the
+// caller's (ctx.h).
 #include <chrono>
 #include <cstddef>
 #include <cmath>
@@ -60,15 +61,6 @@ stag_status check_rational(stag_ctx* c, const stag_rational* r, double mass) {
 stag_status check_common(stag_ctx* c, bool need_gauge) {
     if (!c) return fail(nullptr, STAG_ERR_INVALID_ARG, "handle is NULL");
     if (need_gauge && !c->has_gauge) return fail(c, STAG_ERR_NO_GAUGE, "no gauge field set (call stag_set_gauge)");
-    return STAG_OK;
-}
-
-// order the caller's stream after the internal stream
-stag_status leave(stag_ctx* c) {
-    HIP_OR_FAIL(c, hipGetLastError());
-    HIP_OR_FAIL(c, hipEventRecord(c->ev_out, c->s));
-    HIP_OR_FAIL(c, hipStreamWaitEvent(c->user, c->ev_out, 0));
-    c->inside = false;
     return STAG_OK;
 }
 
@@ -451,9 +443,10 @@ stag_status stag_power_estimate(stag_handle c, double mass, int iters, uint64_t 
     if (e) return e;
     if (!std::isfinite(mass) || iters < 0 || !lam_out)
         return fail(c, STAG_ERR_INVALID_ARG, "need a finite mass, iters >= 0 and lam_out");
-    if ((e = begin_internal(c))) return e;
+    InternalStream on(c);
+    if ((e = on.begin())) return e;
     if ((e = power_rayleigh_impl(c, mass, iters, seed, lam_out))) return e;
-    return leave(c);
+    return on.end();
 }
 
 stag_status stag_check_spectrum(stag_handle c, double mass, double xmin, double xmax, double* lam_out) {
@@ -461,9 +454,10 @@ stag_status stag_check_spectrum(stag_handle c, double mass, double xmin, double 
     if (e) return e;
     if (!std::isfinite(mass) || !std::isfinite(xmin) || !std::isfinite(xmax) || !(xmin < xmax))
         return fail(c, STAG_ERR_INVALID_ARG, "need a finite mass and xmin < xmax");
-    if ((e = begin_internal(c))) return e;
+    InternalStream on(c);
+    if ((e = on.begin())) return e;
     const stag_status chk = spectrum_check_impl(c, mass, xmin, xmax, lam_out);
-    if ((e = leave(c))) return e;
+    if ((e = on.end())) return e;
     return chk;
 }
 
@@ -529,7 +523,8 @@ stag_status solve_entry(stag_handle c, double mass, const stag_rational* r, doub
         if (!(mixed->tol_sloppy > 0.0) || mixed->tol_sloppy >= 1.0 || mixed->reliable_every < 1)
             return fail(c, STAG_ERR_INVALID_ARG, "need 0 < tol_sloppy < 1 and reliable_every >= 1");
     }
-    if ((e = begin_internal(c))) return e;
+    InternalStream on(c);
+    if ((e = on.begin())) return e;
     if ((e = ensure_pool(c, r->n))) return e;
     std::vector<double2*> xs(r->n);
     for (int k = 0; k < r->n; ++k) xs[k] = x ? (double2*)x[k] : pool_vec(c->pool_x, c->g, k);
@@ -547,7 +542,7 @@ stag_status solve_entry(stag_handle c, double mass, const stag_rational* r, doub
         for (int k = 0; k < r->n; ++k) X.p[k] = xs[k];
         launch_rational_sum(c->g, (const double2*)b, X, c->st, (double2*)sum, c->s);
     }
-    if ((e = leave(c))) return e;
+    if ((e = on.end())) return e;
     if (sum) HIP_OR_FAIL(c, hipStreamSynchronize(c->s));
     if (info) {
         info->iters = res.iters;
@@ -611,10 +606,11 @@ stag_status stag_fermion_action(stag_handle c, double mass, const stag_rational*
     if ((e = check_rational(c, r, mass))) return e;
     if (!(tol > 0.0) || maxiter < 1) return fail(c, STAG_ERR_INVALID_ARG, "need tol > 0 and maxiter >= 1");
     if (!aligned16(phi) || !S) return fail(c, STAG_ERR_INVALID_ARG, "phi NULL/misaligned or S_out NULL");
-    if ((e = begin_internal(c))) return e;
+    InternalStream on(c);
+    if ((e = on.begin())) return e;
     SolveResult res;
     if ((e = fermion_action_impl(c, mass, r, tol, maxiter, (const double2*)phi, S, res))) return e;
-    if ((e = leave(c))) return e;
+    if ((e = on.end())) return e;
     if (info) {
         info->iters = res.iters;
         info->n = r->n;
@@ -632,10 +628,11 @@ stag_status stag_fermion_force(stag_handle c, double mass, const stag_rational* 
     if (!(tol > 0.0) || maxiter < 1) return fail(c, STAG_ERR_INVALID_ARG, "need tol > 0 and maxiter >= 1");
     if (!aligned16(phi) || !aligned16(mom)) return fail(c, STAG_ERR_INVALID_ARG, "phi/mom NULL or misaligned");
     if (!std::isfinite(dt)) return fail(c, STAG_ERR_INVALID_ARG, "dt must be finite");
-    if ((e = begin_internal(c))) return e;
+    InternalStream on(c);
+    if ((e = on.begin())) return e;
     SolveResult res;
     if ((e = fermion_force_impl(c, mass, r, tol, maxiter, (const double2*)phi, (double*)mom, dt, res))) return e;
-    if ((e = leave(c))) return e;
+    if ((e = on.end())) return e;
     if (info) {
         info->iters = res.iters;
         info->n = r->n;
@@ -687,7 +684,8 @@ stag_status stag_chiral_condensate(stag_handle c, double mass, double tol, int m
         return fail(c, STAG_ERR_INVALID_ARG, "need mass > 0, tol > 0, maxiter >= 1, n_noise >= 1 and mean_out");
     const double residue = 1.0, pole = 0.0;
     const stag_rational r{1, 0.0, &residue, &pole};
-    if ((e = begin_internal(c))) return e;
+    InternalStream on(c);
+    if ((e = on.begin())) return e;
     const double V = 2.0 * c->g.vh;
     double sum = 0.0, sum2 = 0.0;
     for (int k = 0; k < n_noise; ++k) {
@@ -698,14 +696,14 @@ stag_status stag_chiral_condensate(stag_handle c, double mass, double tol, int m
         double S = 0.0;  // Re <eta, A^-1 eta>
         if ((e = fermion_action_impl(c, mass, &r, tol, maxiter, c->xi, &S, res))) return e;
         if (res.nonfinite || !res.converged) {
-            if ((e = leave(c))) return e;
+            if ((e = on.end())) return e;
             return finish_solve_status(c, res);
         }
         const double v = 4.0 * mass * S / V;
         sum += v;
         sum2 += v * v;
     }
-    if ((e = leave(c))) return e;
+    if ((e = on.end())) return e;
     const double mean = sum / n_noise;
     *mean_out = mean;
     if (err_out)
@@ -807,17 +805,15 @@ stag_status stag_md_trajectory(stag_handle c, const stag_hmc_params* p, stag_tra
     if (ferm && (p->spectrum_lo != 0.0 || p->spectrum_hi != 0.0) &&
         !(std::isfinite(p->spectrum_lo) && std::isfinite(p->spectrum_hi) && p->spectrum_lo < p->spectrum_hi))
         return fail(c, STAG_ERR_INVALID_ARG, "spectrum interval must be finite with lo < hi (or both 0)");
-    if ((e = begin_internal(c))) return e;
+    InternalStream on(c);
+    if ((e = on.begin())) return e;
     const Geom& g = c->g;
     const size_t mb = (size_t)64 * g.vh * sizeof(double);
     const size_t lb = (size_t)72 * g.vh * sizeof(double2);
     // the tables' interval against the spectrum of A on the starting links
     if (ferm && p->spectrum_hi != 0.0) {
         stag_status chk = spectrum_check_impl(c, p->mass, p->spectrum_lo, p->spectrum_hi, nullptr);
-        if (chk) {
-            leave(c);
-            return chk;
-        }
+        if (chk) return chk;
     }
     stag_traj_info I{};
     SolveResult res;
@@ -856,7 +852,6 @@ stag_status stag_md_trajectory(stag_handle c, const stag_hmc_params* p, stag_tra
         launch_copy(c->links, c->links_backup, lb, c->s);
         links_changed(c);
         if (p->surrogate && p->inner_iters > 0) stag_surrogate_set_aux(p->surrogate, nullptr);
-        leave(c);
         return err;
     };
     e = [&]() -> stag_status {
@@ -978,7 +973,7 @@ stag_status stag_md_trajectory(stag_handle c, const stag_hmc_params* p, stag_tra
         links_changed(c);
     }
     if ((e = gauge_action_impl(c, p->beta, nullptr, &I.plaquette))) return e;
-    if ((e = leave(c))) return e;
+    if ((e = on.end())) return e;
     HIP_OR_FAIL(c, hipStreamSynchronize(c->s));
     I.cg_iters_total = iters;
     I.n_solves = nsolve;

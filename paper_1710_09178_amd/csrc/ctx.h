@@ -16,8 +16,7 @@ struct stag_ctx {
     hipStream_t user = nullptr;
     hipStream_t s = nullptr;
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
-    bool inside = false;  // s may hold work that the caller's stream does not wait for yet
-    bool outside = false; // the caller's stream may hold work that s does not wait for yet
+    bool internal = false;  // a call that uses s is under way (InternalStream)
     hipEvent_t chunk_ev[2]{};
     // gauge field: FP64 master copy plus copies derived on demand
     double2* links = nullptr;
@@ -112,28 +111,50 @@ stag_status dmalloc(stag_ctx* c, T** p, size_t bytes) {
     return STAG_OK;
 }
 
-// Orders the internal stream after the caller's; the calls that use it begin so.
-inline stag_status begin_internal(stag_ctx* c) {
-    HIP_OR_FAIL(c, hipSetDevice(c->device));
-    c->inside = true;
-    c->outside = false;
-    HIP_OR_FAIL(c, hipEventRecord(c->ev_in, c->user));
-    HIP_OR_FAIL(c, hipStreamWaitEvent(c->s, c->ev_in, 0));
-    return STAG_OK;
-}
-// The same for the calls of a model, which run on the internal stream without
-// waiting for the caller's other work: they follow the handle's own calls.
-inline stag_status begin_model(stag_ctx* c) {
-    c->inside = true;
-    return c->outside ? begin_internal(c) : STAG_OK;
-}
+// For calls that loop, poll or replay graphs: from begin() on their launches go
+// to the handle's own stream, after the caller's earlier work, and whichever way
+// the call returns (an error among its launches, too) the caller's stream waits
+// for what it has launched.
+class InternalStream {
+    stag_ctx* c;
+    stag_status close() {
+        c->internal = false;
+        HIP_OR_FAIL(c, hipEventRecord(c->ev_out, c->s));
+        HIP_OR_FAIL(c, hipStreamWaitEvent(c->user, c->ev_out, 0));
+        return STAG_OK;
+    }
 
-// For calls whose launches neither loop nor poll: between begin() and the end of
-// the object's life the handle's stream is the caller's own.  On the internal
-// stream such a call pays two event records and two waits between streams, more
-// than its kernels on a small lattice (A psi at 4^4: 31 us there, 8 us here).
-// Calls that use the internal stream begin by waiting for the caller's stream,
-// hence for these launches too.
+   public:
+    explicit InternalStream(stag_ctx* ctx) : c(ctx) {}
+    InternalStream(const InternalStream&) = delete;
+    InternalStream& operator=(const InternalStream&) = delete;
+    ~InternalStream() {
+        if (!c->internal) return;
+        std::string err;  // (the call's own error is the one to report)
+        err.swap(c->err);
+        (void)close();
+        c->err.swap(err);
+    }
+    stag_status begin() {
+        HIP_OR_FAIL(c, hipSetDevice(c->device));
+        HIP_OR_FAIL(c, hipEventRecord(c->ev_in, c->user));
+        HIP_OR_FAIL(c, hipStreamWaitEvent(c->s, c->ev_in, 0));
+        c->internal = true;
+        return STAG_OK;
+    }
+    stag_status end() {
+        HIP_OR_FAIL(c, hipGetLastError());
+        return close();
+    }
+};
+
+// For calls whose launches neither loop nor poll, and those of a model: between
+// begin() and the end of the object's life the handle's stream is the caller's
+// own.  On the internal stream such a call pays two event records and two waits
+// between streams, more than its kernels on a small lattice (A psi at 4^4: 31 us
+// there, 8 us here).  Calls that use the internal stream begin by waiting for the
+// caller's stream, hence for these launches too, and the caller's waits for
+// theirs; within such a call (a trajectory's model) the launches follow its own.
 class CallerStream {
     stag_ctx* c;
     hipStream_t own;
@@ -145,13 +166,7 @@ class CallerStream {
     ~CallerStream() { c->s = own; }
     stag_status begin() {
         HIP_OR_FAIL(c, hipSetDevice(c->device));
-        if (c->inside) {  // (a model's call, or one that failed, left work there)
-            HIP_OR_FAIL(c, hipEventRecord(c->ev_out, own));
-            HIP_OR_FAIL(c, hipStreamWaitEvent(c->user, c->ev_out, 0));
-            c->inside = false;
-        }
-        c->s = c->user;
-        c->outside = true;
+        if (!c->internal) c->s = c->user;
         return STAG_OK;
     }
     stag_status end() {

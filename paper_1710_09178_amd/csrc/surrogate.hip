@@ -735,7 +735,8 @@ stag_status stag_surrogate_add_pair(stag_surrogate_handle s, const void* force) 
     if (s->pairs >= s->capacity) return sfail(s, STAG_ERR_INVALID_ARG, "dataset is full");
     stag_ctx* c = s->lat;
     if (!c->has_gauge) return sfail(s, STAG_ERR_NO_GAUGE, "lattice has no gauge field");
-    if (begin_model(c)) return sfail(s, STAG_ERR_HIP, c->err);
+    CallerStream on(c);
+    if (on.begin()) return sfail(s, STAG_ERR_HIP, c->err);
     features_into(s, s->pairs);
     k_sur_target<<<(int)((s->links + 255) / 256), 256, 0, c->s>>>(c->g, (const double*)force, slot_t(s, s->pairs));
     SHIP(s, hipGetLastError());
@@ -747,7 +748,8 @@ stag_status stag_surrogate_add_pair(stag_surrogate_handle s, const void* force) 
 stag_status stag_surrogate_train(stag_surrogate_handle s, int epochs, double lr, double* loss_out) {
     if (!s || epochs < 0 || !(lr > 0)) return sfail(s, STAG_ERR_INVALID_ARG, "bad arguments");
     if (s->pairs == 0) return sfail(s, STAG_ERR_INVALID_ARG, "no training pairs");
-    if (begin_model(s->lat)) return sfail(s, STAG_ERR_HIP, s->lat->err);
+    CallerStream on(s->lat);
+    if (on.begin()) return sfail(s, STAG_ERR_HIP, s->lat->err);
     double last = 0.0;
     for (int ep = 0; ep < epochs; ++ep) {
         // one Adam step per stored configuration; the loss is summed on the
@@ -770,7 +772,8 @@ stag_status stag_surrogate_eval(stag_surrogate_handle s, const void* force, doub
     stag_ctx* c = s->lat;
     if (!c->has_gauge) return sfail(s, STAG_ERR_NO_GAUGE, "lattice has no gauge field");
     const int k = s->capacity;  // scratch slot
-    if (begin_model(c)) return sfail(s, STAG_ERR_HIP, c->err);
+    CallerStream on(c);
+    if (on.begin()) return sfail(s, STAG_ERR_HIP, c->err);
     features_into(s, k);
     k_sur_target<<<(int)((s->links + 255) / 256), 256, 0, c->s>>>(c->g, (const double*)force, slot_t(s, k));
     train_pass(s, k, s->links, grad_out != nullptr, 0, 0.f);
@@ -786,7 +789,8 @@ stag_status stag_surrogate_force(stag_surrogate_handle s, void* mom, double dt) 
     stag_ctx* c = s->lat;
     if (!c->has_gauge) return sfail(s, STAG_ERR_NO_GAUGE, "lattice has no gauge field");
     const int k = s->capacity;
-    if (begin_model(c)) return sfail(s, STAG_ERR_HIP, c->err);
+    CallerStream on(c);
+    if (on.begin()) return sfail(s, STAG_ERR_HIP, c->err);
     features_into(s, k);
     // four blocks fit a CU; with fewer tiles a wave each
     const long long ntiles = (s->links + 15) / 16;
