@@ -565,6 +565,17 @@ __global__ __launch_bounds__(kBlock) void k_sur_adam(const float* __restrict__ g
     prm[k] -= lr * (mk / c1) / (sqrtf(vk / c2) + eps);
 }
 
+// New parameters from pinned host memory (23 KB, read by the kernel: a copy engine's
+// transfer and the wait for it take 20 us), and the optimiser's start.
+static_assert(NPAR * sizeof(float) % 16 == 0, "copied 16 bytes at a time");
+__global__ __launch_bounds__(kBlock) void k_sur_set(const float* __restrict__ from, float* __restrict__ prm,
+                                                    float* __restrict__ m, float* __restrict__ v) {
+    const int k = blockIdx.x * kBlock + threadIdx.x;
+    if (k >= NPAR) return;
+    prm[k] = from[k];
+    m[k] = v[k] = 0.f;
+}
+
 }  // namespace
 }  // namespace stag
 
@@ -587,6 +598,8 @@ struct stag_surrogate {
     double* lpart = nullptr;
     double* lsum = nullptr;
     double* lsum_host = nullptr;
+    float* prm_host = nullptr;         // pinned [2][NPAR]: parameters on their way in, and out
+    hipEvent_t prm_in = nullptr;       // the last copy in
     int nblocks = 0;
     int adam_t = 0;
     std::string err;
@@ -669,9 +682,14 @@ stag_status stag_surrogate_create(stag_surrogate_handle* out, stag_handle lat, i
         stag_surrogate_destroy(s);
         return e;
     }
-    if (hipHostMalloc((void**)&s->lsum_host, 16, hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc((void**)&s->lsum_host, 16, hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void**)&s->prm_host, 2 * NPAR * 4, hipHostMallocDefault) != hipSuccess) {
         stag_surrogate_destroy(s);
         return STAG_ERR_OOM;
+    }
+    if (hipEventCreateWithFlags(&s->prm_in, hipEventDisableTiming) != hipSuccess) {
+        stag_surrogate_destroy(s);
+        return STAG_ERR_HIP;
     }
     // He-style initial parameters from a seeded host generator (last layer small)
     std::vector<float> p(NPAR, 0.f);
@@ -686,20 +704,29 @@ stag_status stag_surrogate_create(stag_surrogate_handle* out, stag_handle lat, i
     for (int i = 0; i < HD * FI; ++i) p[OW1 + i] = (float)(gauss() * std::sqrt(2.0 / FI));
     for (int i = 0; i < HD * HD; ++i) p[OW2 + i] = (float)(gauss() * std::sqrt(2.0 / HD));
     for (int i = 0; i < NO * HD; ++i) p[OW3 + i] = (float)(gauss() * 0.01);
-    hipMemcpy(s->prm, p.data(), NPAR * 4, hipMemcpyHostToDevice);
-    hipMemset(s->m, 0, NPAR * 4);
-    hipMemset(s->v, 0, NPAR * 4);
+    e = stag_surrogate_params(s, nullptr, p.data());
+    if (e) {
+        lat->err = s->err;
+        stag_surrogate_destroy(s);
+        return e;
+    }
     *out = s;
     return STAG_OK;
 }
 
 stag_status stag_surrogate_destroy(stag_surrogate_handle s) {
     if (!s) return STAG_OK;
+    // (work on the caller's stream ends before hipFree returns)
     if (s->lat && s->lat->s) hipStreamSynchronize(s->lat->s);
+    if (s->prm_in) {
+        hipEventSynchronize(s->prm_in);
+        hipEventDestroy(s->prm_in);
+    }
     void* bufs[] = {s->f, s->B, s->tgt, s->prm, s->m, s->v, s->gpart, s->gpart2, s->grad, s->lpart, s->lsum};
     for (void* b : bufs)
         if (b) hipFree(b);
     if (s->lsum_host) hipHostFree(s->lsum_host);
+    if (s->prm_host) hipHostFree(s->prm_host);
     delete s;
     return STAG_OK;
 }
@@ -708,15 +735,32 @@ const char* stag_surrogate_last_error(stag_surrogate_handle s) { return s ? s->e
 
 int stag_surrogate_param_count(void) { return NPAR; }
 
+// In stream order, like the kernels that read the parameters: set_in is copied to
+// pinned memory before the call returns and from there behind the work before it.
 stag_status stag_surrogate_params(stag_surrogate_handle s, float* get_out, const float* set_in) {
     if (!s) return STAG_ERR_INVALID_ARG;
+    stag_ctx* c = s->lat;
+    CallerStream on(c);
+    if (on.begin()) return sfail(s, STAG_ERR_HIP, c->err);
     if (set_in) {
-        SHIP(s, hipMemcpy(s->prm, set_in, NPAR * 4, hipMemcpyHostToDevice));
-        SHIP(s, hipMemset(s->m, 0, NPAR * 4));
-        SHIP(s, hipMemset(s->v, 0, NPAR * 4));
+        hipStreamCaptureStatus cap;
+        SHIP(s, hipStreamIsCapturing(c->s, &cap));
+        if (cap != hipStreamCaptureStatusNone)
+            return sfail(s, STAG_ERR_HIP, "parameters cannot be set while the stream is captured");
+        SHIP(s, hipEventSynchronize(s->prm_in));
+        std::memcpy(s->prm_host, set_in, NPAR * 4);
+        k_sur_set<<<(NPAR + kBlock - 1) / kBlock, kBlock, 0, c->s>>>(s->prm_host, s->prm, s->m, s->v);
+        SHIP(s, hipGetLastError());
+        SHIP(s, hipEventRecord(s->prm_in, c->s));
         s->adam_t = 0;
     }
-    if (get_out) SHIP(s, hipMemcpy(get_out, s->prm, NPAR * 4, hipMemcpyDeviceToHost));
+    if (get_out) {
+        float* out = s->prm_host + NPAR;
+        launch_copy(out, s->prm, NPAR * 4, c->s);
+        SHIP(s, hipGetLastError());
+        SHIP(s, hipStreamSynchronize(c->s));
+        std::memcpy(get_out, out, NPAR * 4);
+    }
     return STAG_OK;
 }
 

@@ -72,6 +72,41 @@ def test_model_calls_follow_the_callers_kernels(side):
             assert torch.equal(got, ref)
 
 
+@pytest.mark.parametrize("side", [False, True])
+def test_parameters_change_between_the_kernels_that_read_them(side):
+    """Parameters set right after a force are the next force's, and the array
+    they came from is free again when the call returns."""
+    log(f"parameters set behind a force side={side}")
+    dims = (16, 16, 16, 8)
+    stream = torch.cuda.Stream() if side else torch.cuda.default_stream()
+    with torch.cuda.stream(stream):
+        lat, _ = _lattice(dims, stream, 3)
+        sur, mom, slow = stag.Surrogate(lat, 1, seed=5), lat.new_mom(), torch.rand(4096, 4096, device="cuda")
+        params = [sur.get_params(), stag.Surrogate(lat, 1, seed=6).get_params()]
+
+        def forces(sync):
+            out = []
+            for k in range(6):
+                p = params[k % 2].copy()
+                sur.set_params(p)
+                p[:] = float("nan")
+                if sync:
+                    torch.cuda.synchronize()
+                elif k % 3 == 2:
+                    slow @ slow
+                sur.force(mom, 0.0)
+                out.append(mom.clone())
+                if sync:
+                    torch.cuda.synchronize()
+            assert (sur.get_params() == params[1]).all()
+            return out
+
+        ref = forces(True)
+        assert not torch.equal(ref[0], ref[1])
+        for got, exp in zip(forces(False), ref):
+            assert torch.equal(got, exp)
+
+
 def _captured_operator_replays(lat, src, stream):
     a, out, ref = lat.new_vec(), lat.new_vec(), lat.new_vec()
     graph = torch.cuda.CUDAGraph()
