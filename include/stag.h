@@ -540,14 +540,27 @@ stag_status stag_profile_samples(stag_handle h, int kind, float* us_out, int cap
  * whose Dslash grid (Vh / 64 blocks) is at most 512 blocks, where iterations
  * are latency-bound; 2: at every size; 0: never (the three-launch loop).
  * Mode 1 goes one step further on lattices of at most one 64-site tile per
- * compute unit (Vh <= 16384) without the improved operator: the whole solve is
+ * compute unit (Vh <= 16384; two tiles, Vh <= 32768, for FP32 solves and for
+ * the refinement) without the improved operator: the whole solve is
  * one cooperative launch (resident.hip) that keeps the links in registers,
  * unless profiling is on, the launch is refused or a wait inside it exceeds one
- * second (the loop above then does the solve, and the later ones).
+ * second.  The loop above then does the solve and the next 16, after which the
+ * launch is tried again, with less patience; each further failure doubles that
+ * number, up to 1024, and a success ends the matter.
  * All loops solve the same systems to the same tolerance; their reduction
  * trees differ, so results agree to rounding, not bitwise.  Returns
  * STAG_ERR_INVALID_ARG for a mode outside 0..2. */
 stag_status stag_set_fused_iteration(stag_handle h, int mode);
+/* The loops that the latest solve on h ran in: loops[0] of the multi-shift CG,
+ * loops[1] of the refinement of a mixed-precision solve (its last pole's;
+ * STAG_LOOP_NONE for other solves).  Host array of length 2. */
+typedef enum {
+    STAG_LOOP_NONE = 0,
+    STAG_LOOP_THREE_LAUNCH = 1,
+    STAG_LOOP_FUSED = 2,
+    STAG_LOOP_ONE_LAUNCH = 3
+} stag_loop;
+stag_status stag_solve_loops(stag_handle h, int loops[2]);
 /* How every FP64 operator application of h loads the links (and long links):
  * mode 1 (default) with non-temporal loads when the FP64 field(s) exceed
  * the 256 MB of the Infinity Cache -- streaming them past it keeps the shared

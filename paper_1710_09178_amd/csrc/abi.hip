@@ -1086,6 +1086,16 @@ stag_status stag_set_fused_iteration(stag_handle c, int on) {
     return STAG_OK;
 }
 
+// The loops that the latest solve ran in.
+stag_status stag_solve_loops(stag_handle c, int loops[2]) {
+    stag_status e = check_common(c, false);
+    if (e) return e;
+    if (!loops) return fail(c, STAG_ERR_INVALID_ARG, "loops NULL");
+    loops[0] = c->loops[0];
+    loops[1] = c->loops[1];
+    return STAG_OK;
+}
+
 // How the FP64 operator loads its links: 0 plain loads, 1 non-temporal when
 // the field exceeds the Infinity Cache (default), 2 always non-temporal.
 stag_status stag_set_link_streaming(stag_handle c, int mode) {

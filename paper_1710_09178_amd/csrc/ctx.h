@@ -6,6 +6,7 @@
 #include <unordered_map>
 #include <vector>
 
+#include "backoff.h"
 #include "common.h"
 #include "dslash.h"
 
@@ -65,8 +66,9 @@ struct stag_ctx {
     int lag = 8;                         // shift-update window of the multi-shift solver
     int use_graph = 1;                   // replay iteration chunks from captured hipGraphs
     int fused = 1;                       // FP64 solves fold the base update into the D_oe launch
-    int resident = 1;                    // one-launch solves where the lattice fits (0: a wait timed out)
-    unsigned long long res_wait = 100000000;  // ... after this many ticks of the 100 MHz clock
+    stag::Backoff resident;              // one-launch solves where the lattice fits
+    unsigned long long res_wait = 100000000;  // ticks of the 100 MHz clock before a wait in one is given up
+    int loops[2] = {STAG_LOOP_NONE, STAG_LOOP_NONE};  // of the latest solve: multi-shift, refinement
     int link_nt = 1;                     // non-temporal FP64 link loads: 0 never, 1 by field size, 2 always
     // captured iteration chunks, keyed by every argument their launches take
     struct ChunkGraph {

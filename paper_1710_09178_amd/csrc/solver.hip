@@ -568,8 +568,8 @@ uint64_t solve_kind(const MsState* h, bool fused, bool fp64, int naik, int fmt64
 // One launch of the resident solver (resident.hip) on the state in c->st: a new
 // solve of source b, or (b = NULL) max_steps further steps of the CG in r, p.
 // Reads the state back into c->st_host.  done = false: it could not be launched
-// or a wait inside it timed out; c->resident is then off and the outputs are
-// undefined.  after(): work enqueued behind the launch.
+// or a wait inside it timed out; the outputs are then undefined, and the solves
+// that follow do without it for a while.  after(): work enqueued behind the launch.
 template <class V, class After>
 stag_status run_resident(stag_ctx* c, const LinkSet& ls, const double2* b, VecPtrs X, VecPtrs P, int max_steps,
                          After after, bool& done) {
@@ -588,24 +588,24 @@ stag_status run_resident(stag_ctx* c, const LinkSet& ls, const double2* b, VecPt
     a.lag = h->lag;
     a.max_steps = max_steps;
     a.mt = h->mass_term;
-    a.wait = c->res_wait;
+    a.wait = c->resident.patience(c->res_wait);
     done = launch_resident<V>(c->g, ls, a, c->s) == hipSuccess;
     if (!done) (void)hipGetLastError();
     if (done) after();
     HIP_OR_FAIL(c, hipMemcpyAsync(c->st_host, c->st, sizeof(MsState), hipMemcpyDeviceToHost, c->s));
     HIP_OR_FAIL(c, hipStreamSynchronize(c->s));
     done = done && !c->st_host->aborted;
-    if (!done) c->resident = 0;
+    done ? c->resident.worked() : c->resident.failed();
     return STAG_OK;
 }
 
-// Exchange area of the resident solver; false (and off) where it cannot be had.
+// Exchange area of the resident solver; false (and off for a while) where it cannot be had.
 bool ensure_exchange(stag_ctx* c) {
     if (c->xch) return true;
     if (hipMalloc(&c->xch, resident_bytes(c->g)) == hipSuccess) return true;
     (void)hipGetLastError();
     c->xch = nullptr;
-    c->resident = 0;
+    c->resident.failed();
     return false;
 }
 
@@ -613,8 +613,8 @@ bool ensure_exchange(stag_ctx* c) {
 // iteration takes 4-7 us where the fused loop takes 12-14 us (8^4: 5.2 against
 // 11.9 us, 16^3x8: 7.2 against 14.1 us, 12 poles, whole solve over iterations).
 bool resident_ready(stag_ctx* c, const LinkSet& ls, bool fp64, bool refine = false) {
-    return c->fused == 1 && c->lag >= 2 && c->resident && !c->prof_on && resident_fits(c->g, ls, fp64, refine) &&
-           ensure_exchange(c);
+    return c->fused == 1 && c->lag >= 2 && !c->prof_on && resident_fits(c->g, ls, fp64, refine) &&
+           c->resident.use() && ensure_exchange(c);
 }
 
 template <class V>
@@ -635,6 +635,7 @@ stag_status ms_solve_t(stag_ctx* c, const LinkSet& ls, double mass, const stag_r
     constexpr bool fp64 = sizeof(V) == sizeof(double2);
     int base;
     bool solved = false;
+    c->loops[1] = STAG_LOOP_NONE;
     // one launch per solve where the lattice fits the chip, a launch loop
     // otherwise: with window >= 2 (the fused loop keeps r_{j-1} and r_j in the
     // ring at once) the fused one on grids of at most kFusedMaxBlocks Dslash
@@ -645,6 +646,7 @@ stag_status ms_solve_t(stag_ctx* c, const LinkSet& ls, double mass, const stag_r
         HIP_OR_FAIL(c, hipMemcpyAsync(c->st, h, sizeof(MsState), hipMemcpyHostToDevice, c->s));
         res.fused = false;
         if ((e = run_resident<V>(c, ls, b, X, P, -1, []() {}, solved))) return e;
+        c->loops[0] = STAG_LOOP_ONE_LAUNCH;
     }
     if (!solved) {
         init_state(h, n, r->pole, r->residue, r->c0, mass, tol, maxiter, base);
@@ -654,6 +656,7 @@ stag_status ms_solve_t(stag_ctx* c, const LinkSet& ls, double mass, const stag_r
         HIP_OR_FAIL(c, hipMemcpyAsync(c->st, h, sizeof(MsState), hipMemcpyHostToDevice, c->s));
         launch_ms_init<V>(g, b, K.r, K.p, X, P, c->st, c->qpart[0], c->s);
         res.fused = fused;
+        c->loops[0] = fused ? STAG_LOOP_FUSED : STAG_LOOP_THREE_LAUNCH;
         // the iterations of the last solve of this kind, as the chunk scheduler's
         // estimate (a hint only: the solve runs until its own stop)
         const uint64_t kind = solve_kind(h, fused, fp64, c->naik, ls.fmt64, ls.fmt32);
@@ -724,6 +727,7 @@ stag_status refine_pole(stag_ctx* c, const LinkSet& ls, double mass, double pole
         const double one = 1.0;
         init_state(h, 1, &pole, &one, 0.0, mass, tol, maxiter - iters_out, base);
         const bool resident = resident_ready(c, ls, false, true);
+        c->loops[1] = resident ? STAG_LOOP_ONE_LAUNCH : STAG_LOOP_THREE_LAUNCH;
         if (resident) h->lag = 2;  // (no shifts: the window only sizes buffers)
         h->bb_given = 1;
         h->it[0].bb = bb;

@@ -30,6 +30,7 @@ STAG_ERR_OOM = -7
 FIELD_HALF_VEC, FIELD_MOM, FIELD_CANON_HALF_VEC, FIELD_CANON_GAUGE, FIELD_CANON_MOM = range(5)
 LINKS_F64_18, LINKS_F64_12, LINKS_F32_18, LINKS_F16_12 = range(4)
 MAX_POLES = 48
+LOOP_NAMES = ("none", "three-launch", "fused", "one-launch")
 
 
 class StagError(RuntimeError):
@@ -130,6 +131,7 @@ def load_library() -> ctypes.CDLL:
         "stag_set_link_format": (S, [H, I]),
         "stag_set_naik": (S, [H, D, D]),
         "stag_set_fused_iteration": (S, [H, I]),
+        "stag_solve_loops": (S, [H, ctypes.POINTER(I)]),
         "stag_batch_autotune": (S, [H, I, ctypes.c_char_p, ctypes.POINTER(D), ctypes.POINTER(I)]),
         "stag_set_link_streaming": (S, [H, I]),
         "stag_profile_samples": (S, [H, I, ctypes.POINTER(ctypes.c_float), I, ctypes.POINTER(I)]),
@@ -532,6 +534,12 @@ class Lattice:
         """0 / False: three-launch loop; 1 / True (default): one launch per solve on the smallest lattices, fused
         loop on small grids, three launches above; 2: fused loop at every size."""
         self._check(self.lib.stag_set_fused_iteration(self.h, int(mode)))
+
+    def solve_loops(self) -> tuple:
+        """Loops of the latest solve: (multi-shift, refinement of a mixed solve), of LOOP_NAMES."""
+        loops = (ctypes.c_int * 2)()
+        self._check(self.lib.stag_solve_loops(self.h, loops))
+        return tuple(LOOP_NAMES[v] for v in loops)
 
     def set_link_streaming(self, mode: int):
         """0 plain link loads, 1 non-temporal beyond the Infinity Cache (default), 2 always non-temporal."""
