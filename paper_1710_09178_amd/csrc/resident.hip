@@ -239,7 +239,7 @@ struct ResStep {  // scalars of one shift in one step; a frozen shift has {0, 1,
 
 // Eight waves of 8 sites each: lane 16 mu + 8 b + i does the forward (b = 0) or
 // backward hop of direction mu at site i of its wave.  Two waves per SIMD leave
-// a lane 256 registers, of which FP64 uses 228: two tiles per CU (128 registers)
+// a lane 256 registers, of which FP64 uses 226: two tiles per CU (128 registers)
 // spill 165 of them and then lose to the launch loop (16^4: 23.6 against 23.2 us
 // per iteration), and so do the 16 hops per site of the improved operator
 // (16^3x8, 12-real links: 21.3 against 19.1 us).  Both hops of a direction in
@@ -685,8 +685,8 @@ __global__ void k_fill_empty(u4v* __restrict__ p, size_t n) {
         p[i] = u4v{kResEmptyLo, kResEmptyHi, kResEmptyLo, kResEmptyHi};
 }
 
-// Blocks of this kernel that the current device holds at once (asked once per
-// device; 0 where that is unknown).
+// Blocks of this kernel that the current device holds at once, asked until the
+// device has answered; 0 where it does not say.
 constexpr size_t kResHistMax = (size_t)2 * kLagMax * kMaxPoles * sizeof(ResStep);
 constexpr int kResDevices = 64;
 template <class Link, bool SHIFTS, int WAVES>
@@ -701,7 +701,7 @@ int capacity() {
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, (const void*)k_resident<Link, SHIFTS, WAVES>,
                                                      kResThreads, SHIFTS ? kResHistMax : 0) != hipSuccess) {
         (void)hipGetLastError();
-        blocks = 0;
+        return 0;  // (asked again by the next solve)
     }
     known[dev].store(blocks * cus + 1, std::memory_order_relaxed);
     return blocks * cus;
