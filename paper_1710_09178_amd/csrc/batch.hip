@@ -158,11 +158,12 @@ struct BlockSums {
 
 // One block per tile: TPS threads per site split the 4 directions; every
 // thread applies its links to all right-hand sides of the lattice.  At 9 lattices
-// of 70,848 sites together and 4 right-hand sides the four-thread form misses
-// the L2 for 155 MB (storing) and 184 MB (CG epilogue) of the 109 and 136 MB that
-// it cannot do without, at 6 TB/s: 24 and 27 us (26 and 33 us before the tiles
+// of 70,848 sites together and 4 right-hand sides the four-thread form cannot
+// do without 109 MB (storing) and 136 MB (CG epilogue) and misses the L2 for 155
+// and 184 MB, at 6 TB/s: 24 and 27 us (26 and 33 us before the tiles
 // of a lattice were put in neighbour order and the waves finished a right-hand
-// side each).  A fourth wave per SIMD (128 registers, 12 spilled) gains nothing.
+// side each).  156 registers: three waves per SIMD; a fourth (128 registers, 12
+// spilled) gains nothing.
 template <int TPS, class V, class Epi, bool NT, bool L12>
 __global__ __launch_bounds__(kBlock, TPS == 4 ? 3 : 2) void k_bdslash(BatchDev bd, const V* __restrict__ links, const V* __restrict__ in,
                                                     int out_par, Epi epi, const int* __restrict__ inst_done) {
@@ -199,7 +200,7 @@ __global__ __launch_bounds__(kBlock, TPS == 4 ? 3 : 2) void k_bdslash(BatchDev b
             const V* uf = lk + link_off(g, out_par, mu, 0) + cb;
             const V* ub = lk + link_off(g, 1 - out_par, mu, 0) + cbb;
             constexpr int NE = L12 ? 6 : 9;
-            // one matrix at a time, so that four waves fit on a SIMD
+            // one matrix at a time, for its registers
             {
                 V U[9];
 #pragma unroll
@@ -248,8 +249,8 @@ __global__ __launch_bounds__(kBlock, TPS == 4 ? 3 : 2) void k_bdslash(BatchDev b
     }
     if constexpr (kWaveRhs) {
         // The wave of right-hand side r keeps its own slice of it and adds the
-        // other three: a quarter less LDS (36.9 KB: four blocks per CU), and its
-        // sums need no other wave.
+        // other three: a quarter less LDS (36.9 KB), and its sums need no
+        // other wave.
         static_assert(kMaxRhs == 4, "one wave per right-hand side");
 #pragma unroll
         for (int r = 0; r < kMaxRhs; ++r)

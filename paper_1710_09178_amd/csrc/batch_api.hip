@@ -141,8 +141,10 @@ stag_status build_tiles(stag_batch* c) {
 
 BatchDev bdev(const stag_batch* c) {
     // the links of all lattices are streamed from HBM by every operator
-    // application once they exceed what the Infinity Cache keeps (FP64:
-    // 1.2 GB for the 64-lattice batch; the single-lattice operator's rule)
+    // application once they exceed what the Infinity Cache keeps (FP64: 1.2 GB
+    // for the 64-lattice batch).  The line was drawn for single lattices with
+    // plain loads throughout (512 MB; theirs is 256 MB now that they load the
+    // links at a launch's ends plainly); stag_batch_autotune measures both.
     const size_t link_bytes = (size_t)(c->link12 ? 48 : 72) * c->total_vh * 16;
     const int nt = c->link_nt >= 0 ? c->link_nt : (link_bytes > ((size_t)512 << 20) ? 1 : 0);
     return BatchDev{c->inst_d, c->tiles_d, (int)c->tiles_h.size(), kBlock / c->tps, c->nrhs, nt, c->link12};

@@ -14,8 +14,9 @@ namespace stag {
 
 namespace {
 
-// conj(a b - c d); in FP64 with the multiply-adds spelt out, so that every kernel
-// that rebuilds a row, and each of a kernel's kinds of load, rounds alike
+// conj(a b - c d); in FP64 with the multiply-adds spelt out, so that the kernels
+// that read links through this header, and each of their kinds of load, round
+// alike (the batched operator rebuilds its rows with the compiler's contraction)
 __device__ __forceinline__ double2 minor_conj(double2 a, double2 b, double2 c, double2 d) {
     const double x = fma(c.y, d.y, fma(-c.x, d.x, fma(-a.y, b.y, a.x * b.x)));
     const double y = fma(-c.y, d.x, fma(-c.x, d.y, fma(a.y, b.x, a.x * b.y)));

@@ -36,10 +36,13 @@ stag_status ensure_pool(stag_ctx* c, int n) {
 // a launch: D_eo takes the tiles in the opposite order (turned), so it begins with
 // what D_oe ended with, and the next D_oe with what D_eo ended with.  A psi with
 // plain, non-temporal and these loads: 302 MB 100, 114 and 97 us; 453 MB 165, 167
-// and 152; 764 MB (48^3x12) 306, 293 and 280; 1.5 GB 631, 583 and 582.  12-pole
+// and 152; 764 MB (48^3x12) 306, 293 and 280; 1.5 GB 631, 583 and 582, each call
+// behind the last (48^3x12 on its own, or on other fields each time: 294).  12-pole
 // solves against a limit of 512 MB: 302 MB 16.6 against 17.5 ms, 453 MB 33.7
 // against 35.7 ms.  Turning 48 or 96 MB costs up to 2% of that at one end or the
-// other of these sizes, 160 MB 5%.
+// other of these sizes, 160 MB 5%.  The fused loop, where it is asked for at these
+// sizes, streams all links: 302 MB 18.1 ms a solve against 19.8 with plain loads,
+// 453 MB 35.9 against 41.3.
 constexpr size_t kLinkCacheBytes = (size_t)256 << 20;
 constexpr size_t kTurnBytes = (size_t)80 << 20;
 

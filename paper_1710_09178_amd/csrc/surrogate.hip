@@ -260,11 +260,13 @@ __device__ __forceinline__ void forward_tile(const WLds& W, float (*c)[NO], s4 f
 
 // Loss and (GRAD) gradients over a dataset slice.  One wave per 16-link tile
 // (grid-stride); per-wave partial gradients go to gpart[wave][NPAR], partial
-// losses to lpart[wave].  The partition fixes the order of the sums, so there is
-// one wave per SIMD, bound by its own chain of some 1500 instructions per tile
-// (64 of them divisions): 61 us for the 8192 tiles of 16^3x8, and 80 us with the
-// rows read where they are used, operands of the backward pass gathered by
-// halves from rows 128 bytes apart, and accumulators copied round a branch.
+// losses to lpart[wave], one order of the sums for one partition.  The gradients
+// take 320 registers (224, and 96 of the accumulators), hence one wave per SIMD,
+// bound by its own chain of some 1500 instructions per tile (64 of them
+// divisions); held to 256 the compiler spills 125.  61 us for the 8192 tiles of
+// 16^3x8, and 80 us with the rows read where they are used, operands of the
+// backward pass gathered by halves from rows 128 bytes apart, and accumulators
+// copied round a branch.
 template <bool GRAD>
 __global__ __launch_bounds__(64 * kWavesSur) void k_sur_train(const unsigned short* __restrict__ f,
                                                               const float* __restrict__ B,
