@@ -171,6 +171,7 @@ class CallerStream {
         if (!c->internal) c->s = c->user;
         return STAG_OK;
     }
+    hipStream_t internal() const { return own; }
     stag_status end() {
         HIP_OR_FAIL(c, hipGetLastError());
         return STAG_OK;

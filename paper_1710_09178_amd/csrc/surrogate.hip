@@ -601,7 +601,7 @@ struct stag_surrogate {
     double* lsum = nullptr;
     double* lsum_host = nullptr;
     float* prm_host = nullptr;         // pinned [2][NPAR]: parameters on their way in, and out
-    hipEvent_t prm_in = nullptr;       // the last copy in
+    hipEvent_t prm_set = nullptr;      // behind the last launch that set prm
     int nblocks = 0;
     int adam_t = 0;
     std::string err;
@@ -689,7 +689,7 @@ stag_status stag_surrogate_create(stag_surrogate_handle* out, stag_handle lat, i
         stag_surrogate_destroy(s);
         return STAG_ERR_OOM;
     }
-    if (hipEventCreateWithFlags(&s->prm_in, hipEventDisableTiming) != hipSuccess) {
+    if (hipEventCreateWithFlags(&s->prm_set, hipEventDisableTiming) != hipSuccess) {
         stag_surrogate_destroy(s);
         return STAG_ERR_HIP;
     }
@@ -720,9 +720,9 @@ stag_status stag_surrogate_destroy(stag_surrogate_handle s) {
     if (!s) return STAG_OK;
     // (work on the caller's stream ends before hipFree returns)
     if (s->lat && s->lat->s) hipStreamSynchronize(s->lat->s);
-    if (s->prm_in) {
-        hipEventSynchronize(s->prm_in);
-        hipEventDestroy(s->prm_in);
+    if (s->prm_set) {
+        hipEventSynchronize(s->prm_set);
+        hipEventDestroy(s->prm_set);
     }
     void* bufs[] = {s->f, s->B, s->tgt, s->prm, s->m, s->v, s->gpart, s->gpart2, s->grad, s->lpart, s->lsum};
     for (void* b : bufs)
@@ -737,30 +737,36 @@ const char* stag_surrogate_last_error(stag_surrogate_handle s) { return s ? s->e
 
 int stag_surrogate_param_count(void) { return NPAR; }
 
-// In stream order, like the kernels that read the parameters: set_in is copied to
-// pinned memory before the call returns and from there behind the work before it.
+// set_in is copied to pinned memory before the call returns, and from there in
+// stream order, behind the kernels that read the parameters before.  Once that is
+// done (training waits for its own launches) nothing on its way writes them, and
+// they are read beside a force that is under way, on the handle's own stream (one
+// epoch over 4 pairs, a force and the parameters at 16^3x8: 346 us, 366 behind it).
 stag_status stag_surrogate_params(stag_surrogate_handle s, float* get_out, const float* set_in) {
     if (!s) return STAG_ERR_INVALID_ARG;
     stag_ctx* c = s->lat;
     CallerStream on(c);
     if (on.begin()) return sfail(s, STAG_ERR_HIP, c->err);
+    hipStreamCaptureStatus cap;
+    SHIP(s, hipStreamIsCapturing(c->s, &cap));
+    if (cap != hipStreamCaptureStatusNone)
+        return sfail(s, STAG_ERR_HIP, "parameters cannot be set or read while the stream is captured");
     if (set_in) {
-        hipStreamCaptureStatus cap;
-        SHIP(s, hipStreamIsCapturing(c->s, &cap));
-        if (cap != hipStreamCaptureStatusNone)
-            return sfail(s, STAG_ERR_HIP, "parameters cannot be set while the stream is captured");
-        SHIP(s, hipEventSynchronize(s->prm_in));
+        SHIP(s, hipEventSynchronize(s->prm_set));
         std::memcpy(s->prm_host, set_in, NPAR * 4);
         k_sur_set<<<(NPAR + kBlock - 1) / kBlock, kBlock, 0, c->s>>>(s->prm_host, s->prm, s->m, s->v);
         SHIP(s, hipGetLastError());
-        SHIP(s, hipEventRecord(s->prm_in, c->s));
+        SHIP(s, hipEventRecord(s->prm_set, c->s));
         s->adam_t = 0;
     }
     if (get_out) {
         float* out = s->prm_host + NPAR;
-        launch_copy(out, s->prm, NPAR * 4, c->s);
+        const bool done = hipEventQuery(s->prm_set) == hipSuccess;
+        if (!done) (void)hipGetLastError();  // (not ready is no error)
+        const hipStream_t from = done ? on.internal() : c->s;
+        launch_copy(out, s->prm, NPAR * 4, from);
         SHIP(s, hipGetLastError());
-        SHIP(s, hipStreamSynchronize(c->s));
+        SHIP(s, hipStreamSynchronize(from));
         std::memcpy(get_out, out, NPAR * 4);
     }
     return STAG_OK;
