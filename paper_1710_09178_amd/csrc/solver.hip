@@ -63,21 +63,33 @@ stag_status get_links(stag_ctx* c, int fmt32, LinkSet& ls) {
         if (c->link_nt == 1 && ls.nt) ls.turn = (int)(kTurnBytes / (bytes / g.vh));
     }
     stag_status e;
+    // A copy recorded into a caller's graph is made when the graph runs, not now:
+    // the calls that follow make their own.
+    auto made = [&]() {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        return hipStreamIsCapturing(c->s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    };
     if (c->fmt64 == STAG_LINKS_F64_12) {
         if (!c->links_d12 && (e = dmalloc(c, &c->links_d12, l12 * sizeof(double2)))) return e;
-        if (!c->d12_ok) launch_links_to_d12(g, c->links, c->links_d12, c->s);
-        c->d12_ok = true;
+        if (!c->d12_ok) {
+            launch_links_to_d12(g, c->links, c->links_d12, c->s);
+            c->d12_ok = made();
+        }
         ls.d12 = c->links_d12;
     }
     if (fmt32 == STAG_LINKS_F32_18) {
         if (!c->links_s18 && (e = dmalloc(c, &c->links_s18, (size_t)72 * g.vh * sizeof(float2)))) return e;
-        if (!c->s18_ok) launch_links_to_s18(g, c->links, c->links_s18, c->s);
-        c->s18_ok = true;
+        if (!c->s18_ok) {
+            launch_links_to_s18(g, c->links, c->links_s18, c->s);
+            c->s18_ok = made();
+        }
         ls.s18 = c->links_s18;
     } else if (fmt32 == STAG_LINKS_F16_12) {
         if (!c->links_h12 && (e = dmalloc(c, &c->links_h12, l12 * 4))) return e;
-        if (!c->h12_ok) launch_links_to_h12(g, c->links, c->links_h12, c->s);
-        c->h12_ok = true;
+        if (!c->h12_ok) {
+            launch_links_to_h12(g, c->links, c->links_h12, c->s);
+            c->h12_ok = made();
+        }
         ls.h12 = c->links_h12;
     }
     if (!c->naik) return STAG_OK;
@@ -86,24 +98,32 @@ stag_status get_links(stag_ctx* c, int fmt32, LinkSet& ls) {
     ls.c1 = c->naik_c1;
     ls.c3 = c->naik_c3;
     if (!c->long_d18 && (e = dmalloc(c, &c->long_d18, (size_t)72 * g.vh * sizeof(double2)))) return e;
-    if (!c->long_ok) launch_long_links(g, c->links, c->long_d18, c->s);
-    c->long_ok = true;
+    if (!c->long_ok) {
+        launch_long_links(g, c->links, c->long_d18, c->s);
+        c->long_ok = made();
+    }
     ls.ld18 = c->long_d18;
     if (c->fmt64 == STAG_LINKS_F64_12) {
         if (!c->long_d12 && (e = dmalloc(c, &c->long_d12, l12 * sizeof(double2)))) return e;
-        if (!c->long_d12_ok) launch_links_to_d12(g, c->long_d18, c->long_d12, c->s);
-        c->long_d12_ok = true;
+        if (!c->long_d12_ok) {
+            launch_links_to_d12(g, c->long_d18, c->long_d12, c->s);
+            c->long_d12_ok = made();
+        }
         ls.ld12 = c->long_d12;
     }
     if (fmt32 == STAG_LINKS_F32_18) {
         if (!c->long_s18 && (e = dmalloc(c, &c->long_s18, (size_t)72 * g.vh * sizeof(float2)))) return e;
-        if (!c->long_s18_ok) launch_links_to_s18(g, c->long_d18, c->long_s18, c->s);
-        c->long_s18_ok = true;
+        if (!c->long_s18_ok) {
+            launch_links_to_s18(g, c->long_d18, c->long_s18, c->s);
+            c->long_s18_ok = made();
+        }
         ls.ls18 = c->long_s18;
     } else if (fmt32 == STAG_LINKS_F16_12) {
         if (!c->long_h12 && (e = dmalloc(c, &c->long_h12, l12 * 4))) return e;
-        if (!c->long_h12_ok) launch_links_to_h12(g, c->long_d18, c->long_h12, c->s);
-        c->long_h12_ok = true;
+        if (!c->long_h12_ok) {
+            launch_links_to_h12(g, c->long_d18, c->long_h12, c->s);
+            c->long_h12_ok = made();
+        }
         ls.lh12 = c->long_h12;
     }
     return STAG_OK;

@@ -137,6 +137,37 @@ def test_capture_after_model_calls_and_failures():
         _captured_operator_replays(lat, src, stream)
 
 
+@pytest.mark.parametrize("fmt,naik", [(stag.LINKS_F64_12, False), (stag.LINKS_F64_18, True), (stag.LINKS_F64_12, True)])
+def test_operator_beside_a_graph_that_has_not_run(fmt, naik):
+    """The derived links of an operator recorded into a graph are made when the
+    graph runs; the same operator called before that makes its own."""
+    log(f"operator beside a recorded one fmt={fmt} naik={naik}")
+    dims = (8, 6, 4, 10)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        lats = []
+        for _ in range(2):
+            lat, src = _lattice(dims, stream, 4)
+            if naik:
+                lat.set_naik()
+            lat.set_link_format(fmt)
+            lats.append(lat)
+        ref, out, rec = (lats[0].new_vec() for _ in range(3))
+        for k in range(2):
+            lats[0].mdagm(ref, src, 0.1)
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=stream):
+                lats[1].mdagm(rec, src, 0.1)
+            lats[1].mdagm(out, src, 0.1)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, ref) and torch.equal(rec, ref)
+            mom = lats[0].random_momentum(11, k)
+            for lat in lats:
+                lat.link_update(mom, 0.2)
+
+
 def test_model_force_is_captured_with_the_callers_work():
     log("captured model force")
     dims = (8, 6, 4, 10)
